@@ -88,9 +88,12 @@ __global__ __launch_bounds__(NT, 4) void voice_hits_kernel(int L, int Hq, int Hk
     }
     auto insert = [&](double val, int pos) {
         if (val > best[VH_KMAX - 1]) {
+            // from the first entry it exceeds on, every entry moves down one (a displaced value may
+            // equal the next: it stays the earlier of the two)
+            bool move = false;
 #pragma unroll
             for (int s = 0; s < VH_KMAX; ++s)
-                if (val > best[s]) {
+                if (move = move || val > best[s]; move) {
                     const double tv = best[s];
                     const int tp = bpos[s];
                     best[s] = val;
