@@ -5,21 +5,26 @@
 //
 //   voice_hits_kernel   per (answer token, q-head): the K audio positions with the largest
 //                       logit (softmax keeps the order), ties to the lower position, counted
-//                       inside the token's interval.  Logits are exact bf16 products summed in
-//                       double on the matrix cores; a sum of 128 products (16 significant bits
-//                       each) rounds only when their magnitudes span more than ~30 binary
-//                       orders, so the top-K decisions are in practice those of the exact logits.
+//                       inside the token's interval.  voice_screen_kernel finds the candidates on the
+//                       bf16 matrix cores and decides among them in double; voice_hits_kernel takes
+//                       the rows it leaves.  Deciding logits are exact bf16 products summed in
+//                       double; a sum of 128 products (16 significant bits each) rounds only when
+//                       their magnitudes span more than ~30 binary orders, so the top-K decisions are
+//                       in practice those of the exact logits.
 //   key_sens_kernel     per (answer token, KV-head): the mean over audio positions of the L2 norm
 //                       of the key gradient.  A streaming reduction (HBM-bound).
 //   wnw_triage          (host) VS and HS means, VS * HS ranking, roles, normalised importance.
 #include "wnw.h"
 #include "wnw_internal.h"
+#include "wnw_lds.h"
 
+#include <float.h>
 #include <math.h>
 
 #include <algorithm>
 #include <cstring>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 namespace wnw {
@@ -39,6 +44,313 @@ __device__ inline void bf16x2(uint32_t u, double &lo, double &hi)
     hi = (double)__uint_as_float(u & 0xffff0000u);
 }
 
+__device__ inline int vh_xcd_order(int w, int n)
+{
+    const int q = n / 8, r = n % 8, x = w % 8;
+    return x * q + min(x, r) + w / 8;
+}
+
+// Voice hits, screened: the bf16 matrix cores bound every logit, and only the few keys that can
+// be among a row's top K are evaluated in double.  Exactly the integers of voice_hits_kernel (below),
+// which takes the rows that the screen cannot decide (hits = VH_OPEN on return).
+//
+// Bound.  A logit a from v_mfma_f32_32x32x16_bf16 differs from the exact e by at most
+// m = 2^-14 * |q|_1 * max |k|: the products are exact in fp32, and 127 additions that may each lose
+// a unit of the last place (2^-23) of at most sum |q_d k_d| lose under 2^-16 of it; the factor
+// four is margin for the order and alignment inside the instruction.  Keys are split into
+// groups (per lane and register pair) of which the largest a is kept; if T is the K-th
+// largest of these maxima, K different keys have a >= T, hence e >= T - m, so a key of the
+// exact top K, ties included, has a >= T - 2 m.  m uses the largest key element seen up to the
+// key's own tile (and that of the sample, for T's side).
+//   sweep A  every third key (every second for K > 4): T from a sample spread over the audio;
+//   sweep B  every key: those with a >= T - 2 m go to the row's list;
+//   if a list overflowed: both again with T from every key;
+// then the listed keys' logits in double (exact products, 16 lanes a key) and their ranks by
+// (value descending, position ascending).  A row stays open when its list overflows even then
+// (many keys within 2 m of each other, such as a zero query) or its values are not finite, too
+// large or too small for the bound.
+//
+// What bounds it: one 32 x 32 x 128 product per wavefront and tile is 8 matrix instructions against 10 KB
+// read from shared memory and 60 to 110 vector instructions (the scan of sixteen logits, the lists),
+// and a barrier per tile; the keys stream 1.3 to 2 times from HBM (1.2 GB on 240 KV-heads at 15000
+// positions: 0.25 ms at the rate of a large copy).  240 KV-heads, 15000 positions, 256 rows each, K = 4:
+// 4.37 ms with every logit in double, 0.55-0.6 ms here.  Eight wavefronts: RB blocks of 32 rows
+// times KS = 8 / RB shares of a tile's keys, so that a few rows still use the whole work-group.
+constexpr int VH_OPEN = -1;
+constexpr int VF_THREADS = 512;
+constexpr int VF_CAP = 60;       // listed keys per row (60 keep two work-groups of RB = 4 in 160 KB)
+constexpr float VF_GAMMA = 0x1p-14f;
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+
+// Sum over the 16 lanes of a row of lanes (every lane ends with the same sum).
+__device__ inline double sum16d(double v)
+{
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+template <int RB>
+struct VfSmem {
+    static constexpr int KS = 8 / RB;                 // shares of a tile's keys
+    static constexpr int TILE = 32 * KS;              // keys per tile: one 32-key step per wavefront
+    // tiles in shared memory, NBUF - 1 in flight: two work-groups a compute unit for RB = 4
+    static constexpr int NBUF = RB == 1 ? 2 : 3;
+    static constexpr int ROWS = 32 * RB;
+    static constexpr int GRP = 16;                    // group maxima per row and share: 8 per lane, 2 lanes
+    union {
+        alignas(256) uint4 tile[NBUF][TILE * 16];     // see wnw_lds.h
+        float gmax[ROWS][KS * GRP + 1];
+    };
+    int list[ROWS][VF_CAP];
+    int cnt[ROWS];                                    // keys listed (those past VF_CAP are dropped)
+    float thr[ROWS];                                  // T
+    unsigned kmax;                                    // largest key element so far, bf16 magnitude bits
+    int over;
+};
+
+template <int RB>
+__global__ __launch_bounds__(VF_THREADS, RB == 4 ? 4 : 2) void voice_screen_kernel(
+    int L, int Hq, int Hkv, int T, int Ta, int n_tok, int K, const uint16_t *__restrict__ k,
+    const uint16_t *__restrict__ q, const int32_t *__restrict__ span, int32_t *__restrict__ hits)
+{
+    using SM = VfSmem<RB>;
+    constexpr int KS = SM::KS, TILE = SM::TILE, ROWS = SM::ROWS, NBUF = SM::NBUF;
+    constexpr int PF = TILE * 16 / VF_THREADS;        // 16-byte pieces per lane and tile
+    static_assert(PF * VF_THREADS == TILE * 16, "whole pieces per thread");
+    __shared__ SM sm;
+    const int g = Hq / Hkv, R = n_tok * g, nrb = (R + ROWS - 1) / ROWS;
+    const int wg = vh_xcd_order(blockIdx.x, gridDim.x), lk = wg / nrb, rblk = wg - lk * nrb;
+    const int l = lk / Hkv, kv = lk - l * Hkv;
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = wave % RB, ks = wave / RB;         // this wavefront's row block and key share
+    const uint16_t *Kh = k + (size_t)lk * T * D;
+    auto q_row = [&](int r) {                         // row = answer token * g + q-head of the group
+        const int t = r / g, j = r - t * g;
+        return q + (((size_t)t * L + l) * Hq + (size_t)kv * g + j) * D;
+    };
+
+    // B operand: column col = row rblk * ROWS + 32 rw + col; lane half h holds dimensions 16 s + 8 h .. + 8 of step s
+    const int lrow = rw * 32 + col, row = rblk * ROWS + lrow;
+    uint4 qf[8];
+    float q1 = 0.f;
+    {
+        const uint4 *src = (const uint4 *)(row < R ? q_row(row) : q);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            qf[s] = row < R ? src[2 * s + half] : make_uint4(0, 0, 0, 0);
+            const uint32_t d[4] = {qf[s].x, qf[s].y, qf[s].z, qf[s].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                q1 += fabsf(__uint_as_float(d[e] << 16)) + fabsf(__uint_as_float(d[e] & 0xffff0000u));
+        }
+        q1 += __shfl_xor(q1, 32);
+    }
+    if (tid < ROWS) sm.cnt[tid] = 0, sm.thr[tid] = -INFINITY;
+    if (tid == 0) sm.kmax = 0, sm.over = 0;
+
+    float gm[8];                                      // maxima of this lane's groups
+#pragma unroll
+    for (int i = 0; i < 8; ++i) gm[i] = -INFINITY;
+    float thr = -INFINITY, kms = 0.f;                 // T and the sample's largest key element
+
+    const unsigned tile0 = lds_address(&sm.tile[0][0]);
+    const FragOffsets fo(lane);
+    // One sweep over the keys 0, step, 2 step ...; LIST (step 1): append the keys at or above the threshold.
+    // The keys of a tile are looked at one iteration after their product, when the tile's largest
+    // element is known to all wavefronts (each takes a share of the dimensions).
+    auto sweep = [&](auto list_c, int step) {
+        constexpr bool LIST = decltype(list_c)::value;
+        auto look = [&](const f32x16_t &x, int k0) {
+            // x[i]: key k0 + step * (32 ks + 8 (i / 4) + 4 half + i % 4) against row lrow
+            if constexpr (LIST) {
+                // at least the lowest finite value: a masked key (-inf) is never listed
+                const float lim = fmaxf(thr - q1 * VF_GAMMA * (kms + __uint_as_float(*(volatile unsigned *)&sm.kmax << 16)), -FLT_MAX);
+                float mx = x[0];
+#pragma unroll
+                for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[i]);
+                if (__any(mx >= lim)) {
+                    unsigned bits = 0;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) bits |= x[i] >= lim ? 1u << i : 0u;
+                    while (__any(bits != 0)) {
+                        if (bits) {
+                            const int i = __ffs((int)bits) - 1;
+                            bits &= bits - 1;
+                            const int at = atomicAdd(&sm.cnt[lrow], 1);
+                            if (at < VF_CAP) sm.list[lrow][at] = k0 + ks * 32 + 4 * half + 8 * (i >> 2) + (i & 3);
+                        }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) gm[i] = fmaxf(gm[i], fmaxf(x[2 * i], x[2 * i + 1]));
+            }
+        };
+        const int dk = step * TILE, n = (Ta + dk - 1) / dk;
+        const TileLoader<TILE, PF> ld(wave, lane, step);
+        // past the audio the last key comes again (masked below)
+        auto issue = [&](int t, int b) { ld.load(Kh, t * dk, Ta, tile0 + (unsigned)b * (TILE * D * 2)); };
+        __syncthreads();                              // whatever shared the tiles' memory is done
+#pragma unroll
+        for (int b = 0; b < NBUF - 1; ++b) issue(b, b);
+        f32x16_t x;
+        const unsigned frag0 = tile0 + (unsigned)(ks * 32) * (D * 2);
+        int buf = 0;
+        for (int t = 0; t < n; ++t) {
+            lds_loads_wait<(NBUF - 2) * PF>();        // this wavefront's part of tile t has landed
+            lds_tile_barrier();                       // everyone's has, and tile t - 1 is read
+            issue(t + NBUF - 1, buf == 0 ? NBUF - 1 : buf - 1);
+            const int k0 = t * dk;
+            if (t > 0) look(x, k0 - dk);
+            // this wavefront's share of the tile's elements, for their maximum (two bf16 magnitudes a word)
+            u16x2_t mx = {0, 0};
+#pragma unroll
+            for (int j = 0; j < PF; ++j) {
+                const uint4 a = sm.tile[buf][(wave * PF + j) * 64 + lane];
+                const uint32_t d[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2_t, d[e] & 0x7fff7fffu));
+            }
+            const unsigned fb = frag0 + (unsigned)buf * (TILE * D * 2);
+            x = f32x16_t{};
+#pragma unroll
+            for (int s = 0; s < 8; ++s) x = mfma32(frag_read(fb + fo.o[s]), __builtin_bit_cast(bf16x8_t, qf[s]), x);
+            const unsigned m = max((unsigned)mx.x, (unsigned)mx.y);
+            // a new maximum is rare after the first tiles: one ballot otherwise
+            if (__any(m > *(volatile unsigned *)&sm.kmax)) atomicMax(&sm.kmax, m);
+            if (k0 + dk > Ta) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (k0 + step * (ks * 32 + 4 * half + 8 * (i / 4) + i % 4) >= Ta) x[i] = -INFINITY;
+            }
+            buf = buf == NBUF - 1 ? 0 : buf + 1;
+        }
+        lds_loads_wait<0>();                          // the loads past the last tile
+        __syncthreads();
+        look(x, (n - 1) * dk);
+    };
+    // T: the K-th largest of the row's group maxima (-inf while fewer than K groups hold a key)
+    auto threshold = [&] {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sm.gmax[lrow][ks * SM::GRP + half * 8 + i] = gm[i];
+        __syncthreads();
+        // sixteen lanes a row: each ranks its share of the maxima among all
+        for (int r = tid >> 4; r < ROWS; r += VF_THREADS / 16) {
+            for (int a = tid & 15; a < KS * SM::GRP; a += 16) {
+                const float v = sm.gmax[r][a];
+                int gt = 0, ge = 0;
+                for (int b = 0; b < KS * SM::GRP; ++b) {
+                    const float w = sm.gmax[r][b];
+                    gt += w > v;
+                    ge += w >= v;
+                }
+                if (gt < K && ge >= K) sm.thr[r] = v;   // equal maxima write the same value
+            }
+        }
+        __syncthreads();
+        thr = row < R ? sm.thr[lrow] : INFINITY;      // a padding row lists nothing
+        kms = __uint_as_float(sm.kmax << 16);
+    };
+    // The sample's T lets about smp * K keys of a row pass, far under VF_CAP for nearly every row; an
+    // overflow costs the work-group two more sweeps.  A short audio is its own sample.
+    const int smp = Ta < 16 * TILE ? 1 : K <= 4 ? 3 : 2;
+    sweep(std::false_type{}, smp);
+    threshold();
+    sweep(std::true_type{}, 1);
+    __syncthreads();
+    if (smp > 1) {
+        if (tid < ROWS && sm.cnt[tid] > VF_CAP) sm.over = 1;
+        __syncthreads();
+        if (sm.over) {
+            // other groups than the sample's: a key is in one group only
+#pragma unroll
+            for (int i = 0; i < 8; ++i) gm[i] = -INFINITY;
+            sweep(std::false_type{}, 1);
+            threshold();
+            if (tid < ROWS) sm.cnt[tid] = 0;          // before the sweep's first barrier
+            sweep(std::true_type{}, 1);
+            __syncthreads();
+        }
+    }
+    // rows outside the bound's range stay open, as those with too many keys
+    {
+        const float kmax = __uint_as_float(sm.kmax << 16);
+        const bool in_range = sm.kmax < 0x7f80u && kmax >= 0x1p-60f && kmax < 0x1p60f && q1 >= 0x1p-60f && q1 < 0x1p60f;
+        if (ks == 0 && half == 0 && !in_range) sm.cnt[lrow] = VF_CAP + 1;
+    }
+    __syncthreads();
+    // Exact logits of the listed keys: sixteen lanes a row, four keys in flight; lane i keeps the
+    // keys i, i + 16, ... and ranks them among all.
+    const int l16 = tid & 15, base = lane & 48;
+    for (int r = tid >> 4; r < ROWS; r += VF_THREADS / 16) {
+        const int rg = rblk * ROWS + r;
+        if (rg >= R) break;
+        const int t = rg / g, j = rg - t * g, n = sm.cnt[r];
+        int32_t *dst = hits + ((size_t)t * L + l) * Hq + (size_t)kv * g + j;
+        if (n > VF_CAP) {
+            if (l16 == 0) *dst = VH_OPEN;
+            continue;
+        }
+        double qd[8];
+        {
+            const uint4 w = ((const uint4 *)q_row(rg))[l16];
+            const uint32_t d[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bf16x2(d[e], qd[2 * e], qd[2 * e + 1]);
+        }
+        constexpr int NS = (VF_CAP + 15) / 16;
+        double val[NS];
+        int pos[NS], before[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            val[s] = -INFINITY, pos[s] = INT32_MAX, before[s] = 0;
+            for (int u0 = 0; u0 < 16 && s * 16 + u0 < n; u0 += 4) {
+                uint4 w[4];
+                int p[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    p[u] = sm.list[r][min(s * 16 + u0 + u, n - 1)];
+                    w[u] = ((const uint4 *)(Kh + (size_t)p[u] * D))[l16];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t d[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+                    double acc = 0.0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        double a, b;
+                        bf16x2(d[e], a, b);
+                        acc = fma(a, qd[2 * e], acc);
+                        acc = fma(b, qd[2 * e + 1], acc);
+                    }
+                    acc = sum16d(acc);
+                    if (l16 == u0 + u && s * 16 + u0 + u < n) val[s] = acc, pos[s] = p[u];
+                }
+            }
+        }
+#pragma unroll
+        for (int s2 = 0; s2 < NS; ++s2)
+            for (int o = 0; o < 16 && s2 * 16 + o < n; ++o) {
+                const double w = __shfl(val[s2], base + o);
+                const int pw = __shfl(pos[s2], base + o);
+#pragma unroll
+                for (int s = 0; s < NS; ++s) before[s] += w > val[s] || (w == val[s] && pw < pos[s]);
+            }
+        const int a = span[2 * t], b = span[2 * t + 1];
+        int c = 0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) c += s * 16 + l16 < n && before[s] < K && pos[s] >= a && pos[s] < b;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) c += __shfl_xor(c, o);
+        if (l16 == 0) *dst = c;
+    }
+}
+
+// Voice hits in double throughout, for the rows that the screen left open (a work-group whose rows
+// are all decided returns at once).
 // Work-groups: ceil(n_tok * g / VH_ROWS) row blocks per KV-head (row = answer token * g + q-head
 // of the group), in XCD order so that the row blocks of one KV-head read its keys through one L2.
 // Wavefront w owns 16 rows of the block.  The logits run on v_mfma_f64_16x16x4f64 (lane
@@ -49,12 +361,6 @@ __device__ inline void bf16x2(uint32_t u, double &lo, double &hi)
 // four logits of its row (keys k + 4v) and keeps the best eight of the keys it sees (value
 // descending; equal values keep the earlier, lower, position); the four lists of a row (one per
 // lane group) are merged at the end.  Products of bf16 values are exact in double.
-__device__ inline int vh_xcd_order(int w, int n)
-{
-    const int q = n / 8, r = n % 8, x = w % 8;
-    return x * q + min(x, r) + w / 8;
-}
-
 __global__ __launch_bounds__(NT, 4) void voice_hits_kernel(int L, int Hq, int Hkv, int T, int Ta, int n_tok, int K,
                                                        const uint16_t *__restrict__ k, const uint16_t *__restrict__ q,
                                                        const int32_t *__restrict__ span, int32_t *__restrict__ hits)
@@ -64,6 +370,12 @@ __global__ __launch_bounds__(NT, 4) void voice_hits_kernel(int L, int Hq, int Hk
     const int l = lk / Hkv, kv = lk - l * Hkv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kq = lane >> 4, li = lane & 15;
     const int r0 = rblk * VH_ROWS + wave * 16;
+    {
+        const int rg = rblk * VH_ROWS + tid;
+        const int t = rg / g, j = rg - t * g;
+        const bool open = tid < VH_ROWS && rg < R && hits[((size_t)t * L + l) * Hq + (size_t)kv * g + j] == VH_OPEN;
+        if (!__syncthreads_or(open)) return;
+    }
     // B operand: row r0 + li, dimensions 32 kq .. + 32
     double qd[32];
     {
@@ -225,6 +537,28 @@ __global__ __launch_bounds__(KS_THREADS) void key_sens_kernel(int Ta, const floa
     }
 }
 
+// Rows per work-group of the screen: as many of 128, 64, 32 as there are and as leave every compute
+// unit a work-group; fewer rows mean more shares of the keys.
+template <int RB, typename... A>
+hipError_t screen_rb(int64_t R, int64_t heads, hipStream_t st, A... args)
+{
+    using SM = VfSmem<RB>;
+    hipLaunchKernelGGL(voice_screen_kernel<RB>, dim3((unsigned)((R + SM::ROWS - 1) / SM::ROWS * heads)), dim3(VF_THREADS), 0,
+                       st, args...);
+    return hipGetLastError();
+}
+template <typename... A>
+hipError_t launch_voice_screen(int64_t R, int64_t heads, hipStream_t st, A... args)
+{
+    int dev = 0, n_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    if (R > 64 && (R + 127) / 128 * heads >= n_cu) return screen_rb<4>(R, heads, st, args...);
+    if (R > 32 && (R + 63) / 64 * heads >= n_cu) return screen_rb<2>(R, heads, st, args...);
+    return screen_rb<1>(R, heads, st, args...);
+}
+
 thread_local char t_msg[256] = "no error";
 
 wnw_status triage_fail(wnw_status st, const char *msg)
@@ -259,8 +593,13 @@ wnw_status wnw_voice_hits(int32_t layers, int32_t q_heads, int32_t kv_heads, int
         return triage_fail(WNW_ERR_INVALID, "top_k must be in 1..8 and at most audio_len");
     if (n_tok == 0) return WNW_OK;
     if (!k_dev || !q_dev || !span_dev || !hits_dev) return triage_fail(WNW_ERR_INVALID, "NULL pointer");
-    const int64_t nrb = ((int64_t)n_tok * g + VH_ROWS - 1) / VH_ROWS, nwg = nrb * layers * kv_heads;
-    if (nwg > INT32_MAX) return triage_fail(WNW_ERR_UNSUPPORTED, "too many answer tokens for one launch");
+    const int64_t R = (int64_t)n_tok * g, heads = (int64_t)layers * kv_heads;
+    const int64_t nwg = (R + VH_ROWS - 1) / VH_ROWS * heads;
+    if ((R + 31) / 32 * heads > INT32_MAX) return triage_fail(WNW_ERR_UNSUPPORTED, "too many answer tokens for one launch");
+    const hipError_t es = launch_voice_screen(R, heads, (hipStream_t)hip_stream, layers, q_heads, kv_heads, rows, audio_len,
+                                              n_tok, top_k, (const uint16_t *)k_dev, (const uint16_t *)q_dev, span_dev,
+                                              hits_dev);
+    if (es != hipSuccess) return triage_fail(WNW_ERR_HIP, hipGetErrorString(es));
     hipLaunchKernelGGL(voice_hits_kernel, dim3((unsigned)nwg), dim3(NT), 0,
                        (hipStream_t)hip_stream, layers, q_heads, kv_heads, rows, audio_len, n_tok, top_k,
                        (const uint16_t *)k_dev, (const uint16_t *)q_dev, span_dev, hits_dev);

@@ -1,0 +1,77 @@
+"""GPU tests of the kernels that stream tiles straight into shared memory: the voice-hits screen with the
+rows it leaves to the double kernel, at the sizes where it changes path and where tiles end.  Every
+test prints the case it runs before touching the GPU."""
+import numpy as np
+import pytest
+
+from synth import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import oracle as O
+    O.build()
+
+
+HITS = [  # (L, H_q, H_kv, T_a, n_tok, K, what)
+    (32, 16, 8, 1031, 33, 4, ""),           # 128 rows a work-group, a sample of the keys, ragged ends
+    (32, 16, 8, 1024, 40, 8, "dup"),        # the same with keys that tie
+    (32, 16, 8, 70, 33, 8, ""),             # the sample is all keys
+    (32, 16, 8, 2051, 17, 4, ""),           # 64 rows a work-group
+    (2, 8, 8, 4096, 3, 4, ""),              # 32 rows, eight shares of the keys, a sample
+    (1, 24, 8, 4111, 1, 8, "dup"),
+    (1, 8, 2, 129, 1, 1, ""),
+    (1, 8, 2, 1300, 9, 4, "zero"),          # zero queries: every key ties, the list overflows
+    (1, 8, 2, 5000, 9, 8, "same"),          # 200 equal best keys: the list overflows after a sample too
+    (1, 8, 2, 1300, 9, 4, "big"),           # products beyond fp32
+    (1, 8, 2, 1300, 9, 4, "tiny"),          # products below fp32's normal range
+    (1, 8, 2, 1300, 9, 4, "cancel"),        # logits far below their products
+    (1, 8, 2, 1300, 9, 4, "inf"),           # one infinite key element
+]
+
+
+@pytest.mark.parametrize("shape", HITS, ids=[f"L{s[0]}_q{s[1]}_kv{s[2]}_Ta{s[3]}_tok{s[4]}_K{s[5]}{s[6]}" for s in HITS])
+def test_voice_screen_matches_oracle(shape):
+    import torch
+    from oracle import oracle as O
+    from paper_2608_22704_amd import wnw as W
+    from tests.wnw_harness import log, to_dev
+    L, Hq, Hkv, Ta, n_tok, K, what = shape
+    log(f"[case] voice screen {shape}")
+    rng = np.random.default_rng(7 + Ta + n_tok)
+    kf = rng.standard_normal((L, Hkv, Ta + 3, 128), dtype=np.float32)
+    qf = rng.standard_normal((n_tok, L, Hq, 128), dtype=np.float32)
+    kf[:, :, Ta:] *= 100                          # text rows take no part
+    if what == "dup":
+        kf[:, :, 1::5] = kf[:, :, :1]             # a fifth of the keys are one key
+    elif what == "zero":
+        qf[::2] = 0
+    elif what == "same":
+        kf[:, :, 100:4900:24] = kf[:, :, :1] = qf[0, 0, 0] * 2
+    elif what == "big":
+        kf *= np.float32(2e19)
+        qf *= np.float32(1e20)
+    elif what == "tiny":
+        kf *= np.float32(1e-20)
+        qf *= np.float32(1e-19)
+    elif what == "cancel":
+        # q . k = 0 for the bf16 values, up to a small last term
+        h = gen.bf16_to_f32(gen.f32_to_bf16(qf))
+        qf = np.concatenate([h[..., :64], -h[..., :64]], axis=-1)
+        kf[..., 64:] = kf[..., :64]
+        kf[..., 127] += np.float32(0.01) * rng.standard_normal(kf.shape[:-1], dtype=np.float32)
+    k, q = gen.f32_to_bf16(kf), gen.f32_to_bf16(qf)
+    if what == "inf":
+        k[0, 0, 77, 5] = 0x7F80
+    a = rng.integers(0, Ta, size=n_tok)
+    span = np.stack([a, np.minimum(a + rng.integers(1, 1 + Ta // 3, size=n_tok), Ta)], axis=1).astype(np.int32)
+    hits = torch.full((n_tok, L, Hq), -7, dtype=torch.int32, device="cuda")
+    W.wnw_voice_hits(to_dev(k), to_dev(q), torch.from_numpy(span).cuda(), K, Ta, hits)
+    torch.cuda.synchronize()
+    bad = np.argwhere(hits.cpu().numpy() != O.voice_hits(k, q, span, K, Ta))
+    assert not len(bad), f"{len(bad)} of {hits.numel()} differ, first at (token, layer, q-head) {bad[0].tolist()}"
