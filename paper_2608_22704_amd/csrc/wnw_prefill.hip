@@ -5,18 +5,29 @@
 // p[b][l][kv][tau] = sum over the text tokens t and the g q-heads of KV-head kv of the softmax
 // weight that text token t puts on audio position tau; text token t attends to every audio row
 // and to text rows 0..t.  Per KV-head this is S = Q K^T with Q the g * T_t text query rows and K
-// the T_a + T_t key rows, a dense contraction, so both passes run on
-// v_mfma_f32_16x16x32_bf16 (bf16 operands, fp32 accumulation):
-//   pass 1 (prefill_rowstats_kernel): per query row, the log-sum-exp of its logits over its
+// the T_a + T_t key rows, a dense contraction, so both passes run on the bf16 matrix cores (fp32
+// accumulation):
+//   pass 1 (prefill_rowstats_kernel): per query row, 64 minus the log-sum-exp of its logits over its
 //           causal key set (base 2);
 //   pass 2 (prefill_colsum_kernel): per audio key, the sum over all query rows of
 //           exp(s - lse).  Audio keys are visible to every text row, so pass 2 needs no mask.
-// Operand layout of v_mfma_f32_16x16x32_bf16 (wave64): lane l holds A row l % 16 and B column
-// l % 16, each at k = 8 * (l / 16) .. + 8 (of 32); the 16x16 fp32 result holds column l % 16 of
-// rows 4 * (l / 16) + i in element i.
+// The streamed operand of either pass (K rows, then query rows) goes straight from global to shared
+// memory, three 16 KB tiles deep, and the tile loop is unrolled over the three buffers so that no
+// vector instruction computes an address.
+//
+// What bounds it: per logit and pass, an FMA, an exponential and an addition next to 256 flop on the
+// matrix cores, and the chip's power: on 240 KV-heads, 15000 keys and 2048 rows the clock falls to
+// 1.6-1.7 GHz, with the matrix cores busy 57-63 % of the cycles and the vector unit 70 %.  There both
+// passes took 4.06-4.4 ms staged through registers with 16 x 16 products in pass 1, and take 3.45-3.6 ms
+// now (3.8 TFLOP executed: 1.1 PFLOP/s, what a bf16 matrix product of 8192 reaches on the card); on 72
+// KV-heads, 3607 keys and 1176 rows 205-215 us, now 178-187 us.  A loop that takes one product's terms
+// between the next one's matrix instructions, at two work-groups a compute unit, was slower (3.9 ms):
+// three work-groups overlap the two units better.
 #include "wnw_internal.h"
+#include "wnw_lds.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #include <math.h>
 
@@ -24,16 +35,13 @@ namespace wnw {
 
 namespace {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float C2 = 0.08838834764831845f * LOG2E;   // logit scale 1 / sqrt(128), base 2
-constexpr int RS_ROWS = 128;                          // query rows per pass-1 work-group (32 per wave)
-constexpr int CS_KB = 3;                              // 16-key blocks per pass-2 wavefront
-constexpr int CS_KEYS = 4 * 16 * CS_KB;               // audio keys per pass-2 work-group (48 per wave)
-constexpr int TILE = 64;                              // rows staged in LDS per iteration
-constexpr int PADU = D / 8 + 1;                       // uint4 per staged row: 16 + 1 of padding
+constexpr int PT = 64;                                // rows per tile in shared memory
+constexpr int PBUF = 3;                               // tiles in shared memory, two of them in flight
+constexpr int PPF = PT * (D / 8) / NT;                // 16-byte pieces per lane and tile
 
 // 2^x by the hardware instruction alone: outputs below 2^-126 flush to zero (exp2f adds a
 // range fix-up of ~3 instructions per call for them).
@@ -50,26 +58,6 @@ __device__ inline bf16x8_t as_bf8(uint4 u)
 __device__ inline f32x4_t mfma16(bf16x8_t a, bf16x8_t b, f32x4_t c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// A tile of TILE rows of D bf16 goes global -> registers (load, rows >= n read as zero) ->
-// padded LDS rows (store), so the next tile's loads overlap the current tile's arithmetic.
-constexpr int SPT = TILE * (D / 8) / NT;   // 16-byte pieces per thread
-__device__ inline void tile_load(uint4 v[SPT], const uint16_t *src, int r0, int n)
-{
-#pragma unroll
-    for (int j = 0; j < SPT; ++j) {
-        const int i = threadIdx.x + j * NT, r = r0 + (i >> 4);
-        v[j] = r < n ? *(const uint4 *)(src + (size_t)r * D + (i & 15) * 8) : make_uint4(0, 0, 0, 0);
-    }
-}
-__device__ inline void tile_store(uint4 *dst, const uint4 v[SPT])
-{
-#pragma unroll
-    for (int j = 0; j < SPT; ++j) {
-        const int i = threadIdx.x + j * NT;
-        dst[(i >> 4) * PADU + (i & 15)] = v[j];
-    }
 }
 
 // Work-group w is dispatched to accelerator die (XCD) w % 8, each with its own L2.  The
@@ -91,212 +79,216 @@ __device__ inline void merge_ms(float &m, float &l, float m2, float l2)
     l = a + b;
 }
 
-// Pass 1.  Grid: ceil(g * T_t / RS_ROWS) row blocks for each of the B * L * H_kv KV-heads,
-// in XCD order.  Wave w owns query rows
-// r0 + 32 w .. + 32 (two 16-row blocks) of KV-head (b, lk); rows r = j * T_t + t (q-head j of
-// the group, text token t).  Each lane keeps an online (max, sum) for the four rows it holds in
-// the result layout, over the keys of its column; the 16 columns are merged at the end.
-__global__ __launch_bounds__(NT) void prefill_rowstats_kernel(Geometry g, const uint16_t *__restrict__ K,
-                                                             const uint16_t *__restrict__ qt, float *__restrict__ lse)
+// Pass 1.  Grid: ceil(g * T_t / (128 NB)) row blocks for each of the B * L * H_kv KV-heads, in XCD
+// order.  Wave w owns query rows r0 + 32 NB w .. + 32 NB (NB blocks of 32, the B operands, in
+// registers) of KV-head (b, lk); rows r = j * T_t + t (q-head j of the group, text token t).  The
+// result of 32 keys against 32 rows (see wnw_lds.h) leaves every lane sixteen keys of ONE row, so a
+// row's running (max, sum) is a single pair per lane and block; the two lanes of a row merge at the
+// end.  NB = 2 halves the shared-memory reads per product; NB = 1 is for launches of few work-groups
+// (72 KV-heads, 1176 rows, 3754 keys: 112 us with 1, 121 with 2, 146 with 16 x 16 products).
+template <int NB>
+__global__ __launch_bounds__(NT, NB == 2 ? 2 : 3) void prefill_rowstats_kernel(Geometry g, const uint16_t *__restrict__ K,
+                                                                              const uint16_t *__restrict__ qt,
+                                                                              float *__restrict__ stat)
 {
-    const int R = g.G * g.Tt, nrb = (R + RS_ROWS - 1) / RS_ROWS;
+    constexpr int ROWS = 4 * 32 * NB;
+    const int R = g.G * g.Tt, nrb = (R + ROWS - 1) / ROWS;
     const int v = xcd_order(blockIdx.x, gridDim.x), hd = v / nrb, rblk = v - hd * nrb;
     const int b = hd / (g.L * g.Hkv), lk = hd - b * g.L * g.Hkv, l = lk / g.Hkv, kv = lk - l * g.Hkv;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, grp = lane >> 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 31, half = lane >> 5;
     const uint16_t *Kh = K + (size_t)hd * g.T * D;
     const size_t qbase = (((size_t)b * g.L + l) * g.Hq + (size_t)kv * g.G) * g.Tt;
     const uint16_t *Qh = qt + qbase * D;
-    const int rw = rblk * RS_ROWS + wave * 32;
+    const int rw = rblk * ROWS + wave * 32 * NB + col;   // this lane's row of block 0
 
-    bf16x8_t qf[2][4];
+    __shared__ alignas(256) uint4 kbuf[PBUF][PT * (D / 8)];
+    const unsigned tile0 = lds_address(&kbuf[0][0]);
+    const TileLoader<PT, PPF> ld(wave, lane, 1);
+    auto issue = [&](int t, int buf) { ld.load(Kh, t * PT, g.T, tile0 + (unsigned)buf * (PT * D * 2)); };
+    bf16x8_t qf[NB][8];
+    int lim[NB];                                      // causal limit (last visible key) of the row
+    float nm[NB], sum[NB];
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-        const int r = rw + rb * 16 + col;
+    for (int n = 0; n < NB; ++n) {
+        const int r = rw + n * 32;
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-            qf[rb][kk] = as_bf8(r < R ? *(const uint4 *)(Qh + (size_t)r * D + grp * 8 + 32 * kk) : make_uint4(0, 0, 0, 0));
+        for (int s = 0; s < 8; ++s)
+            qf[n][s] = as_bf8(r < R ? *(const uint4 *)(Qh + (size_t)r * D + 16 * s + 8 * half) : make_uint4(0, 0, 0, 0));
+        lim[n] = r < R ? g.Ta + r % g.Tt : -1;
+        nm[n] = INFINITY;
+        sum[n] = 0.f;
     }
-    // causal limit (last visible key) of the rows this lane holds in the result layout
-    int lim[2][4];
-    float nm[2][4], s[2][4];
+    // Statistics are base 2 and scaled, the running maximum kept negated (nm = -m) for the
+    // exponent's FMA.  Every row sum holds a term of at least 2^0, so exponentials that flush
+    // below 2^-126 change nothing.
+    auto take = [&](f32x16_t (&x)[NB], int k0) {
+        if (k0 + 32 <= g.Ta) {
+            // audio keys: every one visible to every row, no mask.  The terms are first taken against
+            // the running maximum as it stands; only when a row's terms add up to more than 2^20 (or
+            // its maximum is still -inf, which gives +inf) does the wavefront raise the maxima and
+            // take the keys again.  Sums stay far inside fp32's range either way.
+            float t[NB], tall = 0.f;
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+            for (int n = 0; n < NB; ++n) {
+                float a[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = rw + rb * 16 + 4 * grp + i;
-            lim[rb][i] = r < R ? g.Ta + r % g.Tt : -1;
-            nm[rb][i] = INFINITY;
-            s[rb][i] = 0.f;
-        }
-
-    __shared__ uint4 kbuf[2][TILE * PADU];
-    uint4 pre[SPT];
-    tile_load(pre, Kh, 0, g.T);
-    tile_store(kbuf[0], pre);
-    __syncthreads();
-    for (int k0 = 0, it = 0; k0 < g.T; k0 += TILE, ++it) {
-        const uint4 *ks = kbuf[it & 1];
-        const bool more = k0 + TILE < g.T;
-        if (more) tile_load(pre, Kh, k0 + TILE, g.T);
-        // logits of the tile: x[rb][kb][i] for row 4 * grp + i of block rb, key k0 + 16 kb + col
-        f32x4_t x[2][TILE / 16];
+                for (int i = 0; i < 4; ++i) a[i] = exp2_hw(fmaf(x[n][i], C2, nm[n]));
 #pragma unroll
-        for (int kb = 0; kb < TILE / 16; ++kb) {
-            bf16x8_t kf[4];
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) kf[kk] = as_bf8(ks[(kb * 16 + col) * PADU + grp + 4 * kk]);
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb) {
-                f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) acc = mfma16(qf[rb][kk], kf[kk], acc);
-                x[rb][kb] = acc;   // unscaled; the scale folds into the exponent's FMA
+                for (int i = 4; i < 16; ++i) a[i & 3] += exp2_hw(fmaf(x[n][i], C2, nm[n]));
+                t[n] = (a[0] + a[1]) + (a[2] + a[3]);
+                tall += t[n];
             }
-        }
-        // Statistics are base 2 and scaled, the running maximum kept negated (nm = -m) for the
-        // exponent's FMA.  Every row sum holds a term of at least 2^0, so exponentials that flush
-        // below 2^-126 change nothing.
-        if (k0 + TILE <= g.Ta) {
-            // audio tile: every key visible to every row, no mask.  The terms are first taken
-            // against the running maximum as it stands; only when a row's terms add up to more
-            // than 2^20 (or its maximum is still -inf, which gives +inf) does the wavefront raise
-            // the maxima and take the tile again.  Sums stay far inside fp32's range either way.
-            float t[2][4], tall = 0.f;
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float acc = exp2_hw(fmaf(x[rb][0][i], C2, nm[rb][i]));
-#pragma unroll
-                    for (int kb = 1; kb < TILE / 16; ++kb) acc += exp2_hw(fmaf(x[rb][kb][i], C2, nm[rb][i]));
-                    t[rb][i] = acc;
-                    tall += acc;
-                }
             if (__any(tall > 0x1p20f)) {
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
+                for (int n = 0; n < NB; ++n) {
+                    float mt = x[n][0];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float mt = fmaxf(fmaxf(x[rb][0][i], x[rb][1][i]), fmaxf(x[rb][2][i], x[rb][3][i]));
-                        const float mn = fmaxf(-nm[rb][i], mt * C2);
-                        float acc = s[rb][i] * exp2_hw(-nm[rb][i] - mn);   // 0 before the first tile
+                    for (int i = 1; i < 16; ++i) mt = fmaxf(mt, x[n][i]);
+                    const float mn = fmaxf(-nm[n], mt * C2);
+                    float acc = sum[n] * exp2_hw(-nm[n] - mn);   // 0 before the first tile
 #pragma unroll
-                        for (int kb = 0; kb < TILE / 16; ++kb) acc += exp2_hw(fmaf(x[rb][kb][i], C2, -mn));
-                        s[rb][i] = acc;
-                        nm[rb][i] = -mn;
-                    }
+                    for (int i = 0; i < 16; ++i) acc += exp2_hw(fmaf(x[n][i], C2, -mn));
+                    sum[n] = acc;
+                    nm[n] = -mn;
+                }
             } else {
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) s[rb][i] += t[rb][i];
+                for (int n = 0; n < NB; ++n) sum[n] += t[n];
             }
         } else {
-            // keys past a row's causal limit (text rows after its token, rows past the end, keys
-            // past the cache) drop out
+            // keys past a row's causal limit (text rows after its token, rows past the end, keys past
+            // the cache) drop out
 #pragma unroll
-            for (int kb = 0; kb < TILE / 16; ++kb) {
-                const int key = k0 + kb * 16 + col;
+            for (int n = 0; n < NB; ++n) {
+                float mt = -INFINITY;
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (key > lim[rb][i]) x[rb][kb][i] = -INFINITY;
-            }
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float mt = x[rb][0][i];
-#pragma unroll
-                    for (int kb = 1; kb < TILE / 16; ++kb) mt = fmaxf(mt, x[rb][kb][i]);
-                    if (mt == -INFINITY) continue;   // every key of the tile masked for this row
-                    const float mn = fmaxf(-nm[rb][i], mt * C2);
-                    float acc = s[rb][i] * exp2_hw(-nm[rb][i] - mn);   // exp2(-inf) = 0 for an empty row
-#pragma unroll
-                    for (int kb = 0; kb < TILE / 16; ++kb) acc += exp2_hw(fmaf(x[rb][kb][i], C2, -mn));
-                    s[rb][i] = acc;
-                    nm[rb][i] = -mn;
+                for (int i = 0; i < 16; ++i) {
+                    if (k0 + 8 * (i / 4) + 4 * half + i % 4 > lim[n]) x[n][i] = -INFINITY;
+                    mt = fmaxf(mt, x[n][i]);
                 }
-        }
-        if (more) tile_store(kbuf[(it + 1) & 1], pre);
-        __syncthreads();
-    }
-    // merge the 16 columns of each row (lanes of one group), in a fixed order
+                if (mt == -INFINITY) continue;           // every key masked for this row
+                const float mn = fmaxf(-nm[n], mt * C2);
+                float acc = sum[n] * exp2_hw(-nm[n] - mn);   // exp2(-inf) = 0 for an empty row
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float m = -nm[rb][i], l = s[rb][i];
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) {
-                const float m2 = __shfl_xor(m, o), l2 = __shfl_xor(l, o);
-                merge_ms(m, l, m2, l2);
+                for (int i = 0; i < 16; ++i) acc += exp2_hw(fmaf(x[n][i], C2, -mn));
+                sum[n] = acc;
+                nm[n] = -mn;
             }
-            const int r = rw + rb * 16 + 4 * grp + i;
-            if (col == 0 && r < R) lse[qbase + r] = m + log2f(l);
         }
+    };
+    const int nt = (g.T + PT - 1) / PT;
+#pragma unroll
+    for (int i = 0; i < PBUF - 1; ++i) issue(i, i);
+    const FragOffsets fo(lane);
+    // one tile; `buf` is a constant, so every shared address is a lane's offset and an immediate
+    auto tile = [&](int t, auto buf_c) {
+        constexpr int buf = decltype(buf_c)::value;
+        lds_loads_wait<(PBUF - 2) * PPF>();           // this wavefront's part of tile t has landed
+        lds_tile_barrier();                           // everyone's has, and tile t - 1 is read
+        issue(t + PBUF - 1, buf == 0 ? PBUF - 1 : buf - 1);
+#pragma unroll
+        for (int h = 0; h < PT / 32; ++h) {
+            f32x16_t x[NB] = {};
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const bf16x8_t a = frag_read(tile0 + fo.o[s] + (unsigned)(buf * PT + h * 32) * (D * 2));
+#pragma unroll
+                for (int n = 0; n < NB; ++n) x[n] = mfma32(a, qf[n][s], x[n]);
+            }
+            take(x, t * PT + h * 32);
+        }
+    };
+    for (int t = 0; t < nt; t += PBUF) {
+        tile(t, std::integral_constant<int, 0>{});
+        if (t + 1 < nt) tile(t + 1, std::integral_constant<int, 1>{});
+        if (t + 2 < nt) tile(t + 2, std::integral_constant<int, 2>{});
+    }
+    static_assert(PBUF == 3, "the loop above names the buffers");
+    lds_loads_wait<0>();                              // the loads past the last tile
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        float m = -nm[n], s = sum[n];
+        const float m2 = __shfl_xor(m, 32), s2 = __shfl_xor(s, 32);
+        merge_ms(m, s, m2, s2);
+        const int r = rw + n * 32;
+        if (half == 0 && r < R) stat[qbase + r] = (64.f - m) - log2f(s);
+    }
 }
 
-// Pass 2.  Grid: ceil(T_a / CS_KEYS) key blocks for each of the B * L * H_kv KV-heads, in XCD
-// order.  Wave w owns audio keys k0 + 48 w .. + 48 (three 16-key blocks, their K fragments held
-// in registers, so each query fragment read from LDS feeds three MFMA chains); the work-group
-// walks every query row of the KV-head in tiles of TILE rows staged in LDS with their
-// log-sum-exp, and each lane adds exp2(s * C2 - lse) over the rows it holds for its key column.
+// Pass 2.  Grid: ceil(T_a / (64 KB)) key blocks for each of the B * L * H_kv KV-heads, in XCD order.
+// Wave w owns audio keys k0 + 16 KB w .. + 16 KB (KB 16-key blocks, their K fragments held in
+// registers, so each query fragment read from shared memory feeds KB MFMA chains); the work-group
+// walks every query row of the KV-head in tiles of PT rows, and each lane adds exp2(s * C2 - lse) over
+// the rows it holds for its key column.  v_mfma_f32_16x16x32_bf16 here: lane l holds A row l % 16 and B
+// column l % 16 at k = 8 * (l / 16) .. + 8 (of 32); the 16x16 result holds column l % 16 of rows
+// 4 * (l / 16) + i in element i, so a key's sum ends in four lanes (32 x 32 blocks leave it in 32: 118
+// against 107 us on 72 KV-heads, 3607 keys, 1176 rows).
+// KB = 4 feeds more products per fragment read; KB = 3 cuts a small cache into more work-groups
+// (measured, both passes together: 240 KV-heads, 15000 keys, 2048 rows 3.59 ms with 4, 3.66 with 3; 72
+// KV-heads, 3607 keys, 1176 rows 192 us with 4, 187 with 3).
+template <int KB>
 __global__ __launch_bounds__(NT, 3) void prefill_colsum_kernel(Geometry g, const uint16_t *__restrict__ K,
-                                                           const uint16_t *__restrict__ qt,
-                                                           const float *__restrict__ lse, float *__restrict__ p)
+                                                               const uint16_t *__restrict__ qt,
+                                                               const float *__restrict__ stat, float *__restrict__ p)
 {
-    const int R = g.G * g.Tt, nkb = (g.Ta + CS_KEYS - 1) / CS_KEYS;
+    constexpr int KEYS = 64 * KB;
+    const int R = g.G * g.Tt, nkb = (g.Ta + KEYS - 1) / KEYS;
     const int v = xcd_order(blockIdx.x, gridDim.x), hd = v / nkb, kblk = v - hd * nkb;
     const int b = hd / (g.L * g.Hkv), lk = hd - b * g.L * g.Hkv, l = lk / g.Hkv, kv = lk - l * g.Hkv;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, grp = lane >> 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, grp = lane >> 4;
     const uint16_t *Kh = K + (size_t)hd * g.T * D;
     const size_t qbase = (((size_t)b * g.L + l) * g.Hq + (size_t)kv * g.G) * g.Tt;
     const uint16_t *Qh = qt + qbase * D;
-    const int kw = kblk * CS_KEYS + wave * 16 * CS_KB;
+    const int kw = kblk * KEYS + wave * 16 * KB;
 
-    bf16x8_t kf[CS_KB][4];
+    // Each wavefront loads its own copy of a tile's row statistics too, straight to shared memory like
+    // the tile (a load into registers would make the compiler wait for the tiles in flight as well).
+    __shared__ alignas(256) uint4 qbuf[PBUF][PT * (D / 8)];
+    __shared__ alignas(16) float sbuf[PBUF][4][PT];
+    static_assert(PT == 64, "one row statistic per lane and tile");
+    const unsigned tile0 = lds_address(&qbuf[0][0]), stat0 = lds_address(&sbuf[0][wave][0]);
+    const TileLoader<PT, PPF> ld(wave, lane, 1);
+    auto issue = [&](int t, int buf) {
+        ld.load(Qh, t * PT, R, tile0 + (unsigned)buf * (PT * D * 2));
+        load_word_to_lds(stat + qbase, (unsigned)min(t * PT + lane, R - 1) * 4, stat0 + (unsigned)buf * (unsigned)sizeof(sbuf[0]));
+    };
+    bf16x8_t kf[KB][4];
 #pragma unroll
-    for (int kb = 0; kb < CS_KB; ++kb) {
+    for (int kb = 0; kb < KB; ++kb) {
         const int key = kw + kb * 16 + col;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
             kf[kb][kk] = as_bf8(key < g.Ta ? *(const uint4 *)(Kh + (size_t)key * D + grp * 8 + 32 * kk)
                                            : make_uint4(0, 0, 0, 0));
     }
-    float acc[CS_KB] = {};
-    __shared__ uint4 qbuf[2][TILE * PADU];
-    __shared__ float sbuf[2][TILE];
-    uint4 pre[SPT];
-    float pl = 0.f;
-    // Terms are taken as 2^(x - lse + 64) and the sum scaled by 2^-64 at the end, so that terms
-    // below 2^-126 still count without the exponential's range fix-up (terms are at most 1 and
-    // sums of at most R of them stay far below the fp32 range).  sbuf holds 64 - lse; a padding
-    // row holds -inf and adds 0.
-    auto lse_of = [&](int r) { return r < R ? 64.f - lse[qbase + r] : -INFINITY; };
-    tile_load(pre, Qh, 0, R);
-    tile_store(qbuf[0], pre);
-    if (threadIdx.x < TILE) sbuf[0][threadIdx.x] = lse_of(threadIdx.x);
-    __syncthreads();
-    for (int r0 = 0, it = 0; r0 < R; r0 += TILE, ++it) {
-        const uint4 *qs = qbuf[it & 1];
-        const float *sst = sbuf[it & 1];
-        const bool more = r0 + TILE < R;
-        if (more) {
-            tile_load(pre, Qh, r0 + TILE, R);
-            if (threadIdx.x < TILE) pl = lse_of(r0 + TILE + threadIdx.x);
-        }
+    // byte offsets of this lane's four fragments of tile rows 0 .. 15 (rows 16 n .. are 16 n rows further)
+    unsigned fo[4];
 #pragma unroll
-        for (int rb = 0; rb < TILE / 16; ++rb) {
+    for (int kk = 0; kk < 4; ++kk) fo[kk] = (unsigned)(col * (D * 2) + ((4 * kk + grp) ^ col) * 16);
+    float acc[KB] = {};
+    // Terms are taken as 2^(x - lse + 64), with 64 - lse from pass 1, and the sum scaled by 2^-64 at the
+    // end, so that terms below 2^-126 still count without the exponential's range fix-up (terms are at
+    // most 1 and sums of at most R of them stay far below the fp32 range).
+    const int nt = (R + PT - 1) / PT;
+#pragma unroll
+    for (int i = 0; i < PBUF - 1; ++i) issue(i, i);
+    // one tile; `buf` is a constant, so every shared address is a lane's offset and an immediate
+    auto tile = [&](int t, auto buf_c) {
+        constexpr int buf = decltype(buf_c)::value;
+        lds_loads_wait<(PBUF - 2) * (PPF + 1)>();     // this wavefront's part of tile t has landed
+        if (t * PT + PT > R && t * PT + lane >= R) sbuf[buf][wave][lane] = -INFINITY;   // past the last row: adds 0
+        lds_tile_barrier();                           // everyone's has, and tile t - 1 is read
+        issue(t + PBUF - 1, buf == 0 ? PBUF - 1 : buf - 1);
+#pragma unroll
+        for (int rb = 0; rb < PT / 16; ++rb) {
             bf16x8_t qf[4];
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[kk] = as_bf8(qs[(rb * 16 + col) * PADU + grp + 4 * kk]);
-            float st[4];
+            for (int kk = 0; kk < 4; ++kk) qf[kk] = frag_read(tile0 + fo[kk] + (unsigned)(buf * PT + rb * 16) * (D * 2));
+            const f32x4_t st = *(const f32x4_t *)&sbuf[buf][wave][rb * 16 + 4 * grp];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) st[i] = sst[rb * 16 + 4 * grp + i];
-#pragma unroll
-            for (int kb = 0; kb < CS_KB; ++kb) {
+            for (int kb = 0; kb < KB; ++kb) {
                 f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) sc = mfma16(qf[kk], kf[kb][kk], sc);
@@ -304,20 +296,21 @@ __global__ __launch_bounds__(NT, 3) void prefill_colsum_kernel(Geometry g, const
                 for (int i = 0; i < 4; ++i) acc[kb] += exp2_hw(fmaf(sc[i], C2, st[i]));
             }
         }
-        if (more) {
-            tile_store(qbuf[(it + 1) & 1], pre);
-            if (threadIdx.x < TILE) sbuf[(it + 1) & 1][threadIdx.x] = pl;
-        }
-        __syncthreads();
+    };
+    for (int t = 0; t < nt; t += PBUF) {
+        tile(t, std::integral_constant<int, 0>{});
+        if (t + 1 < nt) tile(t + 1, std::integral_constant<int, 1>{});
+        if (t + 2 < nt) tile(t + 2, std::integral_constant<int, 2>{});
     }
+    lds_loads_wait<0>();                              // the loads past the last tile
 #pragma unroll
-    for (int kb = 0; kb < CS_KB; ++kb) {
+    for (int kb = 0; kb < KB; ++kb) {
         acc[kb] += __shfl_xor(acc[kb], 16);
         acc[kb] += __shfl_xor(acc[kb], 32);
     }
     if (grp == 0)
 #pragma unroll
-        for (int kb = 0; kb < CS_KB; ++kb) {
+        for (int kb = 0; kb < KB; ++kb) {
             const int key = kw + kb * 16 + col;
             if (key < g.Ta) p[(size_t)hd * g.Ta + key] = ldexpf(acc[kb], -64);
         }
@@ -445,13 +438,21 @@ hipError_t launch_prefill_scores(const Geometry &g, const uint16_t *K, const uin
         return hipGetLastError();
     }
     const long long nheads = (long long)g.B * g.L * g.Hkv;
-    const long long n1 = (long long)((R + RS_ROWS - 1) / RS_ROWS) * nheads;
-    const long long n2 = (long long)((g.Ta + CS_KEYS - 1) / CS_KEYS) * nheads;
-    if (n1 > INT32_MAX || n2 > INT32_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(prefill_rowstats_kernel, dim3((unsigned)n1), dim3(NT), 0, st, g, K, q_text, lse);
+    // pass 1: work-groups of 256 rows; of 128 where they would leave the device short
+    const long long n1 = (long long)((R + 255) / 256) * nheads, n1s = (long long)((R + 127) / 128) * nheads;
+    // pass 2: KB = 4 from eight work-groups a compute unit up
+    const long long n2 = (long long)((g.Ta + 255) / 256) * nheads, n2s = (long long)((g.Ta + 191) / 192) * nheads;
+    if (n1s > INT32_MAX || n2s > INT32_MAX) return hipErrorInvalidValue;
+    if (n1 >= 4LL * std::max(g.n_cu, 1))
+        hipLaunchKernelGGL(prefill_rowstats_kernel<2>, dim3((unsigned)n1), dim3(NT), 0, st, g, K, q_text, lse);
+    else
+        hipLaunchKernelGGL(prefill_rowstats_kernel<1>, dim3((unsigned)n1s), dim3(NT), 0, st, g, K, q_text, lse);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(prefill_colsum_kernel, dim3((unsigned)n2), dim3(NT), 0, st, g, K, q_text, (const float *)lse, p);
+    if (n2 >= 8LL * std::max(g.n_cu, 1))
+        hipLaunchKernelGGL(prefill_colsum_kernel<4>, dim3((unsigned)n2), dim3(NT), 0, st, g, K, q_text, (const float *)lse, p);
+    else
+        hipLaunchKernelGGL(prefill_colsum_kernel<3>, dim3((unsigned)n2s), dim3(NT), 0, st, g, K, q_text, (const float *)lse, p);
     return hipGetLastError();
 }
 

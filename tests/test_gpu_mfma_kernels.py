@@ -1,6 +1,6 @@
 """GPU tests of the kernels that stream tiles straight into shared memory: the voice-hits screen with the
-rows it leaves to the double kernel, at the sizes where it changes path and where tiles end.  Every
-test prints the case it runs before touching the GPU."""
+rows it leaves to the double kernel, and both passes of the prefill scores, at the sizes where they
+change path and where tiles end.  Every test prints the case it runs before touching the GPU."""
 import numpy as np
 import pytest
 
@@ -75,3 +75,50 @@ def test_voice_screen_matches_oracle(shape):
     torch.cuda.synchronize()
     bad = np.argwhere(hits.cpu().numpy() != O.voice_hits(k, q, span, K, Ta))
     assert not len(bad), f"{len(bad)} of {hits.numel()} differ, first at (token, layer, q-head) {bad[0].tolist()}"
+
+
+PREFILL = [  # (L, H_q, H_kv, T_a, T_t, query scale)
+    (32, 32, 8, 200, 193, 1.0),      # 256 rows and keys a work-group would suffice: pass 1 with two blocks
+    (32, 16, 8, 2049, 9, 1.0),       # pass 2 with four blocks, one key past a work-group
+    (1, 8, 2, 31, 33, 1.0),          # every key block holds text
+    (2, 6, 2, 64, 1, 1.0),           # one text row, whole tiles
+    (1, 8, 1, 161, 64, 1.0),         # audio ends one key into a block of 32
+    (1, 4, 4, 1, 130, 1.0),          # one audio key
+    (1, 8, 2, 515, 70, 12.0),        # logits of hundreds: the running maximum is raised again and again
+]
+
+
+@pytest.mark.parametrize("shape", PREFILL, ids=[f"L{s[0]}_q{s[1]}_kv{s[2]}_Ta{s[3]}_Tt{s[4]}_x{s[5]:g}" for s in PREFILL])
+def test_prefill_scores_match_oracle(shape):
+    import torch
+    from oracle import oracle as O
+    from paper_2608_22704_amd import wnw as W
+    from tests.wnw_harness import log, to_dev
+    L, Hq, Hkv, Ta, Tt, scale = shape
+    log(f"[case] prefill scores {shape}")
+    rng = np.random.default_rng(Ta * 7 + Tt)
+    G, T, D = Hq // Hkv, Ta + Tt, 128
+    k = gen.f32_to_bf16(rng.standard_normal((1, L, Hkv, T, D), dtype=np.float32))
+    q = gen.f32_to_bf16(np.float32(scale) * rng.standard_normal((1, L, Hq, Tt, D), dtype=np.float32))
+    kd = to_dev(k)
+    cfg = W.make_config(1, L, Hq, Hkv, Ta, Tt, 32, 2000)
+    ctx = W.wnw_init_cache(cfg, kd, kd)
+    try:
+        sc = torch.full((1, L, Hkv, Ta), -1.0, dtype=torch.float32, device="cuda")
+        W.wnw_prefill_scores(ctx, to_dev(q), sc)
+        torch.cuda.synchronize()
+        got = sc.cpu().numpy()[0]
+    finally:
+        W.wnw_destroy(ctx)
+    heads = [(l, h) for l in range(L) for h in range(Hkv)]
+    for l, h in heads if len(heads) <= 4 else [heads[i] for i in (0, len(heads) // 2 + 1, len(heads) - 1)]:
+        c1 = O.make_cfg(1, 1, G, 1, D, Ta, Tt, 32, 2000)
+        ref = O.prefill_scores(c1, k[:, l:l + 1, h:h + 1], q[:, l:l + 1, h * G:(h + 1) * G])[0, 0, 0]
+        # A term's exponent (base 2) is a logit x minus the row's log-sum-exp, about max |x|, plus 64: a few
+        # roundings of values up to 64 + 2 max |x| (the products' sums, the scale, the statistic, the FMA)
+        x = gen.bf16_to_f32(q[0, l, h * G:(h + 1) * G].reshape(-1, D)) @ gen.bf16_to_f32(k[0, l, h]).T
+        top = float(np.abs(x).max()) / np.sqrt(D) * np.log2(np.e)
+        tol = 8 * 2.0 ** -24 * (64 + 2 * top)
+        rel = np.abs(got[l, h] - ref) / np.maximum(ref, 2.0 ** -100)   # terms below 2^-190 flush
+        log(f"[prefill] head ({l},{h}): max rel err {rel.max():.3g} of {tol:.3g}")
+        assert (rel <= tol).all()
