@@ -155,7 +155,9 @@ typedef struct {
                                   end of the select kernel).  Near zero in steps that run them
                                   inside the tidal/fixed launch (WNW_F_SELECT_NEXT_STEP with
                                   WNW_F_RECALL_MEMCPY, after a previous-step recall of at most
-                                  4 MiB): t_tidal_fixed_ms holds them then                      */
+                                  4 MiB): t_tidal_fixed_ms holds them then; and on small caches
+                                  without that pair of flags, whose first launch runs them
+                                  (t_anchor_ms)                                                 */
     double t_tidal_fixed_ms;   /* the tidal/fixed launch after the selection.  Same-step timing:
                                   fixed heads, tidal kept rows, complements already on the
                                   device (default recall: also the recall and the attention over

@@ -624,6 +624,16 @@ wnw_status wait_copies(wnw_ctx *c, int par, hipStream_t s)
     return WNW_OK;
 }
 
+// Whether a step runs the mass merge and the selection inside the launch of its anchor tiles: while
+// those tiles all fit the chip at once (two work-groups a compute unit), so that the wait of each
+// for its stores and its arrival delays no tile behind it (on 2928 tiles that wait cost the launch
+// 7 us, as much as it saves).  With next-step timing and host-issued copies the selection has the
+// tidal/fixed launch to run in.
+bool select_with_anchors(const Geometry &g, bool memcpy_path)
+{
+    return !(g.next_step && memcpy_path) && (int64_t)g.n_tiles_a * g.nA * g.B <= 2ll * g.n_cu && anchor_select_fits(g);
+}
+
 // The recall thread's loop (see wnw_ctx::RecallJob).
 void recall_thread(wnw_ctx *c)
 {
@@ -760,7 +770,7 @@ void free_all(wnw_ctx *c)
                     c->scores_int, c->sel_int,
                     c->s.pa_m, c->s.pa_l, c->s.pa_o, c->s.pa_mass, c->s.mass, c->s.a_stat, c->s.ps_m, c->s.ps_l, c->s.ps_o,
                     c->s.streak, c->s.slot_of, c->s.slot_last, c->s.att, c->s.slot_data, c->s.slot_busy, c->s.slot_since,
-                    c->s.step, c->s.kept_list, c->s.new_list, c->s.counts, c->s.arrive, c->s.stats};
+                    c->s.step, c->s.kept_list, c->s.new_list, c->s.counts, c->s.arrive, c->s.arrive_head, c->s.stats};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (c->host_comp) (void)hipHostFree(c->host_comp);
@@ -909,6 +919,7 @@ wnw_status build_tiers(wnw_ctx *c, const uint8_t *keep_all)
     ALLOC(s.new_list, 2 * B * g.knew * 2, "new lists");
     ALLOC(s.counts, 2 * B * 2, "counts");
     ALLOC(s.arrive, B, "arrival counters");
+    ALLOC(s.arrive_head, B * g.nA, "tile arrival counters");
     ALLOC(s.stats, 8, "stats");
 #undef ALLOC
     const size_t host_bytes = B * g.nc * (size_t)g.chunk_elems * sizeof(uint16_t);
@@ -1088,6 +1099,7 @@ wnw_status build_tiers(wnw_ctx *c, const uint8_t *keep_all)
     HIPCHECK(c, hipMemset(s.step, 0, B * sizeof(int32_t)));
     HIPCHECK(c, hipMemset(s.counts, 0, 2 * B * 2 * sizeof(int32_t)));
     HIPCHECK(c, hipMemset(s.arrive, 0, B * sizeof(int32_t)));
+    if (g.nA) HIPCHECK(c, hipMemset(s.arrive_head, 0, B * g.nA * sizeof(int32_t)));
     HIPCHECK(c, hipMemset(s.stats, 0, 8 * sizeof(unsigned long long)));
     HIPCHECK(c, hipDeviceSynchronize());
     c->full_k = c->full_v = nullptr;
@@ -1317,10 +1329,20 @@ wnw_status wnw_decode_step(wnw_ctx *c, const void *q_dev, void *out, float *scor
     // once the selection is done, never behind copies still running on the side streams
     sn.pub = memcpy_path ? c->d_newinfo + (size_t)par * c->mirror_ints : nullptr;
     sn.pub_tag = pub_tag(c->steps);
+    SelectArgs sa{};
+    sa.s = sn;
+    sa.s.arrive = c->s.arrive;
+    sa.scores = sc;
+    sa.ovr = c->override_sel;
+    sa.selected = sel;
+    // A small cache runs the chunk-mass merge and the selection inside the launch of its anchor tiles (the
+    // last tile of a head merges, the last head of a sequence selects): two launches fewer.
+    const bool sel_with_anchors = select_with_anchors(g, memcpy_path);
+    const SelectArgs *saa = sel_with_anchors ? &sa : nullptr;
     if (g.next_step)
-        HIPCHECK(c, launch_attention(g, c->t, sb, q, s0, e0, e1));
+        HIPCHECK(c, launch_attention(g, c->t, sb, q, s0, e0, e1, saa));
     else
-        HIPCHECK(c, launch_anchor(g, c->t, sb, q, s0, e0, e1));
+        HIPCHECK(c, launch_anchor(g, c->t, sb, q, s0, e0, e1, saa));
     // Next-step timing with host-issued copies: the chunk-mass merge and the selection run inside
     // the tidal/fixed launch (its first work-groups, beside the slot items) when the previous
     // step recalled little.  That launch waits for the previous step's copies, and so would the
@@ -1329,7 +1351,7 @@ wnw_status wnw_decode_step(wnw_ctx *c, const void *q_dev, void *out, float *scor
     // step's and the link stays busy.  The host reads the previous step's recall size from its
     // mirror once the recall thread has issued it (the attention launch runs meanwhile).
     bool sel_in_tidal = false;
-    if (g.next_step && memcpy_path && tidal_select_fits(g)) {
+    if (g.next_step && memcpy_path && !sel_with_anchors && tidal_select_fits(g)) {
         int64_t prev_bytes = 0;
         if (c->rec_pending) {
             wnw_status r = recall_wait_issued(c, (int64_t)c->steps - 1);
@@ -1340,7 +1362,7 @@ wnw_status wnw_decode_step(wnw_ctx *c, const void *q_dev, void *out, float *scor
         sel_in_tidal = prev_bytes <= SEL_IN_TIDAL_BYTES;
     }
     c->sel_in_tidal += sel_in_tidal ? 1 : 0;
-    if (!sel_in_tidal) {
+    if (!sel_in_tidal && !sel_with_anchors) {
         HIPCHECK(c, launch_anchor_mass(g, sb, s0));
         HIPCHECK(c, launch_select(g, sn, sc, c->override_sel, sel, s0));
     }
@@ -1382,14 +1404,6 @@ wnw_status wnw_decode_step(wnw_ctx *c, const void *q_dev, void *out, float *scor
             items = ((long long)nmax * g.comp_max + TILE_S - 1) / TILE_S;
         }
         // markers 2 and 3: the launch's own start and end
-        SelectArgs sa{};
-        if (sel_in_tidal) {
-            sa.s = sn;
-            sa.s.arrive = c->s.arrive;
-            sa.scores = sc;
-            sa.ovr = c->override_sel;
-            sa.selected = sel;
-        }
         HIPCHECK(c, launch_tidal_fixed(g, c->t, sb, q, false, false, items, s0, timing ? ev.e[2] : nullptr,
                                        timing ? ev.e[3] : nullptr, sel_in_tidal ? &sa : nullptr));
         // the final merge is queued before the host waits for the selection below, so that the

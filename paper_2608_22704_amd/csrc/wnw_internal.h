@@ -124,6 +124,8 @@ struct StepBuffers {
     int32_t *counts;            // [B][2] kept-list entries (next-step timing: kept + new), new
     int32_t *arrive;            // [B] the selection in the tidal/fixed launch: anchor heads whose chunk
                                 // masses are merged, per sequence (zero between launches); else null
+    int32_t *arrive_head;       // [B][nA] the selection in the anchor tiles' launch: tiles done, per anchor head
+                                // (zero between launches)
     int32_t *pub;               // host-issued recall: mapped pinned mirror of counts [B][2], new
                                 // lists [B][knew][2] and publication tags [B], written by the select
                                 // kernel; else null
@@ -136,21 +138,25 @@ struct StepBuffers {
     const int32_t *seg_rows;    // [B][nc] complement rows of a segment over the tidal heads
 };
 
-// The selection as part of the next-step tidal/fixed launch: the select kernel's arguments, s
-// with the lists the selection writes and the arrival counters.
+// The selection as part of the next-step tidal/fixed launch or of the anchor tiles' launch: the select
+// kernel's arguments, s with the lists the selection writes and the arrival counters.
 struct SelectArgs {
     StepBuffers s;
     float *scores;
     const int32_t *ovr;
     int32_t *selected;
-    int n_mass;                 // work-groups that merge chunk masses (set by the launcher)
+    int n_mass;                 // tidal/fixed launch: work-groups that merge chunk masses (set by the launcher)
 };
 
 // Launchers (wnw_kernels.hip).  Each returns the launch status.  Where a launcher takes two
 // events (either may be null), they are bound to the kernel's own dispatch and carry its start
 // and end times (hipExtLaunchKernel), or are recorded back to back when there is nothing to launch.
+// With sel, the launch also merges the anchor heads' chunk masses and runs the selection, in place of
+// launch_anchor_mass and launch_select (needs anchor_select_fits(g)); launch_attention likewise.
 hipError_t launch_anchor(const Geometry &g, const Tiers &t, const StepBuffers &s, const uint16_t *q,
-                         hipStream_t st, hipEvent_t e0, hipEvent_t e1);
+                         hipStream_t st, hipEvent_t e0, hipEvent_t e1, const SelectArgs *sel = nullptr);
+// Whether the shared memory of an anchor tile's work-group holds the mass merge and the selection of g.
+bool anchor_select_fits(const Geometry &g);
 // Anchor normalisers and chunk masses (the selection's input); the anchor output rows are merged
 // by launch_subset_combine at the end of the step.
 hipError_t launch_anchor_mass(const Geometry &g, const StepBuffers &s, hipStream_t st);
@@ -179,7 +185,7 @@ hipError_t launch_tidal_fixed(const Geometry &g, const Tiers &t, const StepBuffe
 bool tidal_select_fits(const Geometry &g);
 // Anchor attention + chunk mass together with the static tidal/fixed tiles (next-step timing).
 hipError_t launch_attention(const Geometry &g, const Tiers &t, const StepBuffers &s, const uint16_t *q, hipStream_t st,
-                            hipEvent_t e0, hipEvent_t e1);
+                            hipEvent_t e0, hipEvent_t e1, const SelectArgs *sel = nullptr);
 // Next-step timing: copy of the complements listed for recall from mapped pinned memory into
 // their slots, no attention (they are attended from the next step on).
 hipError_t launch_recall(const Geometry &g, const Tiers &t, const StepBuffers &s, hipStream_t st);

@@ -11,7 +11,8 @@
 //                   chunk masses (summed over its q-heads), for the selection.
 //   scores          per chunk: fixed-order sum over anchor q-heads / chunk length (mean).
 //   select          one work-group per sequence: top-k by (score desc, id asc), streaks,
-//                   residency, slot assignment, kept/new lists.
+//                   residency, slot assignment, kept/new lists.  On small caches the anchor tiles' own
+//                   launch runs the mass merge and the selection (select_after_tile).
 //   tidal_fixed     tidal and fixed heads over their kept rows + text, and tidal heads over the
 //                   complements already in their slots (fp32 logits).
 //                   With same-step timing its first work-groups recall: they copy newly resident
@@ -214,6 +215,23 @@ __device__ inline double ld_agent(const double *p)
 {
     return __hip_atomic_load(const_cast<double *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// A value for a later launch (plain), or also for another work-group of this one (AGENT).
+template <bool AGENT>
+__device__ inline void st_stat(double *p, double v)
+{
+    if constexpr (AGENT)
+        st_agent(p, v);
+    else
+        *p = v;
+}
+template <bool AGENT>
+__device__ inline double ld_stat(const double *p)
+{
+    if constexpr (AGENT)
+        return ld_agent(p);
+    else
+        return *p;
+}
 
 template <int G>
 struct AnchorSmem {
@@ -224,7 +242,8 @@ struct AnchorSmem {
     double wm[WAVES * G], wl[WAVES * G];
 };
 
-template <int G>
+// AGENT: the tile's statistics and masses are read by another work-group of the same launch.
+template <int G, bool AGENT>
 __device__ inline void anchor_tile(const Geometry &g, const Tiers &t, const StepBuffers &s, const uint16_t *__restrict__ q,
                                    int tile, int ai, int b, AnchorSmem<G> &sm)
 {
@@ -391,8 +410,8 @@ __device__ inline void anchor_tile(const Geometry &g, const Tiers &t, const Step
         for (int w = 1; w < WAVES; ++w) M = fmax(M, wm[w * G + tid]);
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) L += wl[w * G + tid];
-        s.pa_m[pidx * G + tid] = M;
-        s.pa_l[pidx * G + tid] = L;
+        st_stat<AGENT>(&s.pa_m[pidx * G + tid], M);
+        st_stat<AGENT>(&s.pa_l[pidx * G + tid], L);
     }
     for (int idx = tid; idx < G * D; idx += NT) {
         float o = 0.f;
@@ -414,7 +433,7 @@ __device__ inline void anchor_tile(const Geometry &g, const Tiers &t, const Step
                 const int r0 = t0 + w * RW;
                 if (r0 >= c * g.cl && r0 < (c + 1) * g.cl && r0 < g.Ta) acc2 += wl[w * G + h];
             }
-            s.pa_mass[pidx * G * g.maxc + tid] = acc2;
+            st_stat<AGENT>(&s.pa_mass[pidx * G * g.maxc + tid], acc2);
         }
         return;
     }
@@ -430,16 +449,8 @@ __device__ inline void anchor_tile(const Geometry &g, const Tiers &t, const Step
             for (int rr = r0 + k; rr < r1; rr += 16) acc2 += xs[h * TILE_A + (rr - t0)];
         }
         acc2 = sum16(acc2);
-        if (valid && k == 0) s.pa_mass[pidx * G * g.maxc + grp] = acc2;
+        if (valid && k == 0) st_stat<AGENT>(&s.pa_mass[pidx * G * g.maxc + grp], acc2);
     }
-}
-
-template <int G>
-__global__ __launch_bounds__(NT, G <= 4 ? 4 : 2) void anchor_attn_kernel(Geometry g, Tiers t, StepBuffers s,
-                                                                         const uint16_t *__restrict__ q)
-{
-    __shared__ AnchorSmem<G> sm;
-    anchor_tile<G>(g, t, s, q, blockIdx.x, blockIdx.y, blockIdx.z, sm);
 }
 
 constexpr int COMBINE_THREADS = 1024;
@@ -456,26 +467,6 @@ __device__ inline void store_out(void *out, size_t i, float v, bool bf16)
     static_cast<uint16_t *>(out)[i] = (uint16_t)r;
 }
 
-// Block-wide max / sum of G values per thread (THREADS threads, in double).
-template <int G, int THREADS>
-__device__ inline void block_reduce_g(double v[G], bool is_max, double (*red)[G])
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-        v[h] = is_max ? wave_max(v[h]) : wave_sum(v[h]);
-        if (lane == 0) red[wave][h] = v[h];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-        double m = red[0][h];
-        for (int w = 1; w < THREADS / 64; ++w) m = is_max ? fmax(m, red[w][h]) : m + red[w][h];
-        v[h] = m;
-    }
-    __syncthreads();
-}
-
 constexpr int MASS_THREADS = 256;
 
 // Chunk masses of one anchor KV-head (the part of the anchor merge that the selection needs):
@@ -485,84 +476,78 @@ constexpr int MASS_THREADS = 256;
 // Shared memory of anchor_mass_head besides fac[G][n_tiles_a].
 template <int G>
 struct MassSmem {
-    double red[MASS_THREADS / 64][G];
     double inv_l[G];
 };
 
 // One anchor KV-head ai of sequence b, MASS_THREADS threads; fac: [G][n_tiles_a] doubles of
-// shared memory.
+// shared memory.  Every q-head has LPH lanes of one wavefront, which take its tiles in turn, so that the
+// maximum and the sum are reductions inside the wavefront and a thread takes a few exponentials (with a
+// thread per tile and all G heads in it, eight-head groups spent 8.5 us here, mostly on eight
+// exponentials and sixteen work-group reductions).
 static_assert(MASS_THREADS == NT, "the attention launch's work-groups merge the chunk masses");
-template <int G>
+template <int G, bool AGENT>
 __device__ inline void anchor_mass_head(const Geometry &g, const StepBuffers &s, int ai, int b, double *fac,
                                         MassSmem<G> &ms)
 {
-    const int tid = threadIdx.x;
-    auto &red = ms.red;
+    constexpr int LPH = G <= 4 ? 64 : 32, PF = 128 / LPH;
+    static_assert(G * LPH <= MASS_THREADS, "lanes for every q-head");
+    const int tid = threadIdx.x, hh = tid / LPH, ln = tid % LPH;
     double *inv_l = ms.inv_l;
     const int nt = g.n_tiles_a;
     const size_t base = ((size_t)b * g.nA + ai) * nt;
     // a segment of at most MAX_CHUNK positions spans at most MAXT tiles
     constexpr int MAXT = (MAX_CHUNK + TILE_A - 2) / TILE_A + 1;
-    // every load of the first round (this thread's tile maxima and sums, its segment's mass
+    // every load of the first round (this lane's tile maxima and sums, its segment's mass
     // partials) is issued before any is used: one memory round trip for caches of up to
-    // MASS_THREADS tiles and segments
-    double pm[G], pl[G], v[G][MAXT];
+    // 128 tiles and MASS_THREADS segments
+    double pm[PF], pl[PF], v[G][MAXT];
     const int c0 = tid, t_lo0 = c0 < g.nc ? (c0 * g.cl) / TILE_A : 0;
     const int t_hi0 = c0 < g.nc ? (min((c0 + 1) * g.cl, g.Ta) - 1) / TILE_A : -1;
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-        pm[h] = tid < nt ? s.pa_m[(base + tid) * G + h] : -INFINITY;
-        pl[h] = tid < nt ? s.pa_l[(base + tid) * G + h] : 0.0;
+    for (int u = 0; u < PF; ++u) {
+        const int i = ln + u * LPH;
+        const bool on = hh < G && i < nt;
+        pm[u] = on ? ld_stat<AGENT>(&s.pa_m[(base + i) * G + hh]) : -INFINITY;
+        pl[u] = on ? ld_stat<AGENT>(&s.pa_l[(base + i) * G + hh]) : 0.0;
     }
 #pragma unroll
     for (int u = 0; u < MAXT; ++u) {
         const int i = t_lo0 + u, j = c0 - (i * TILE_A) / g.cl;
 #pragma unroll
-        for (int h = 0; h < G; ++h) v[h][u] = i <= t_hi0 ? s.pa_mass[((base + i) * G + h) * g.maxc + j] : 0.0;
+        for (int h = 0; h < G; ++h) v[h][u] = i <= t_hi0 ? ld_stat<AGENT>(&s.pa_mass[((base + i) * G + h) * g.maxc + j]) : 0.0;
     }
-    double m[G], l[G];
+    if (hh < G) {   // whole wavefronts, or the upper half of one with its lower half
+        double M = pm[0], L = 0.0;
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-        m[h] = pm[h];
-        if (tid < nt) fac[h * nt + tid] = pm[h];
-    }
-    for (int i = tid + MASS_THREADS; i < nt; i += MASS_THREADS)
+        for (int u = 1; u < PF; ++u) M = fmax(M, pm[u]);
+        for (int i = ln + PF * LPH; i < nt; i += LPH) M = fmax(M, ld_stat<AGENT>(&s.pa_m[(base + i) * G + hh]));
 #pragma unroll
-        for (int h = 0; h < G; ++h) {
-            const double x = s.pa_m[(base + i) * G + h];
-            fac[h * nt + i] = x;
-            m[h] = fmax(m[h], x);
+        for (int o = 1; o < LPH; o <<= 1) M = fmax(M, __shfl_xor(M, o));
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int i = ln + u * LPH;
+            if (i < nt) {
+                const double f = (M > -INFINITY && pm[u] > -INFINITY) ? exp(pm[u] - M) : 0.0;
+                fac[hh * nt + i] = f;
+                L += pl[u] * f;
+            }
         }
-    block_reduce_g<G, MASS_THREADS>(m, true, red);
+        for (int i = ln + PF * LPH; i < nt; i += LPH) {
+            const double mi = ld_stat<AGENT>(&s.pa_m[(base + i) * G + hh]);
+            const double f = (M > -INFINITY && mi > -INFINITY) ? exp(mi - M) : 0.0;
+            fac[hh * nt + i] = f;
+            L += ld_stat<AGENT>(&s.pa_l[(base + i) * G + hh]) * f;
+        }
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-        l[h] = 0.0;
-        if (tid < nt) {
-            const double f = (m[h] > -INFINITY && pm[h] > -INFINITY) ? exp(pm[h] - m[h]) : 0.0;
-            fac[h * nt + tid] = f;
-            l[h] = pl[h] * f;
+        for (int o = 1; o < LPH; o <<= 1) L += __shfl_xor(L, o);
+        if (ln == 0) {
+            const double inv = L > 0.0 ? 1.0 / L : 0.0;
+            inv_l[hh] = inv;
+            s.a_stat[(((size_t)b * g.nA + ai) * G + hh) * 2] = M;
+            s.a_stat[(((size_t)b * g.nA + ai) * G + hh) * 2 + 1] = inv;
         }
     }
-    for (int i = tid + MASS_THREADS; i < nt; i += MASS_THREADS)
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            const double mi = fac[h * nt + i];
-            const double f = (m[h] > -INFINITY && mi > -INFINITY) ? exp(mi - m[h]) : 0.0;
-            fac[h * nt + i] = f;
-            l[h] += s.pa_l[(base + i) * G + h] * f;
-        }
-    block_reduce_g<G, MASS_THREADS>(l, false, red);   // also publishes fac[]
-    if (tid < G) {
-        double M = m[0], L = l[0];
-#pragma unroll
-        for (int h = 1; h < G; ++h)
-            if (tid == h) M = m[h], L = l[h];
-        const double inv = L > 0.0 ? 1.0 / L : 0.0;
-        inv_l[tid] = inv;
-        s.a_stat[(((size_t)b * g.nA + ai) * G + tid) * 2] = M;
-        s.a_stat[(((size_t)b * g.nA + ai) * G + tid) * 2 + 1] = inv;
-    }
-    __syncthreads();
+    __syncthreads();   // fac[] and inv_l[]
     double *mass = s.mass + ((size_t)b * g.nA + ai) * (size_t)g.nc;
     for (int c = c0; c < g.nc; c += MASS_THREADS) {
         const int t_lo = (c * g.cl) / TILE_A, t_hi = (min((c + 1) * g.cl, g.Ta) - 1) / TILE_A;
@@ -571,7 +556,7 @@ __device__ inline void anchor_mass_head(const Geometry &g, const StepBuffers &s,
             for (int u = 0; u < MAXT; ++u) {
                 const int i = t_lo + u, j = c - (i * TILE_A) / g.cl;
 #pragma unroll
-                for (int h = 0; h < G; ++h) v[h][u] = i <= t_hi ? s.pa_mass[((base + i) * G + h) * g.maxc + j] : 0.0;
+                for (int h = 0; h < G; ++h) v[h][u] = i <= t_hi ? ld_stat<AGENT>(&s.pa_mass[((base + i) * G + h) * g.maxc + j]) : 0.0;
             }
         }
         double acc = 0.0;
@@ -592,7 +577,7 @@ __global__ __launch_bounds__(MASS_THREADS) void anchor_mass_kernel(Geometry g, S
 {
     extern __shared__ double fac[];      // [G][n_tiles_a]
     __shared__ MassSmem<G> ms;
-    anchor_mass_head<G>(g, s, blockIdx.x, blockIdx.y, fac, ms);
+    anchor_mass_head<G, false>(g, s, blockIdx.x, blockIdx.y, fac, ms);
 }
 
 // Output rows of one anchor KV-head's G q-heads from the tile partials and the normalisers
@@ -678,6 +663,78 @@ struct SelectShared {
     int last;
 };
 
+
+// The k chunks with the largest ranking keys, by one wavefront for itself (each of the first TOPK_WAVES
+// wavefronts finds the same ones and writes its share of the flags): 64 R keys in registers, the k-th
+// largest score built two bits at a time from ballots (no barrier), equal scores to the lower ids.
+constexpr int TOPK_WAVES = 4;
+template <int R>
+__device__ inline void top_k_wave(const unsigned long long *ckey, int nk, int k, int *fsel)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = min((int)blockDim.x >> 6, TOPK_WAVES);
+    if (wave >= nwave) return;
+    unsigned key[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) key[r] = r * 64 + lane < nk ? (unsigned)(ckey[r * 64 + lane] >> 32) : 0u;
+    unsigned kth = 0;
+    for (int bit = 30; bit >= 0; bit -= 2) {
+        int n[4] = {k, 0, 0, 0};                      // keys at or above kth with 1, 2 and 3 in these bits
+#pragma unroll
+        for (int d = 1; d < 4; ++d)
+#pragma unroll
+            for (int r = 0; r < R; ++r) n[d] += (int)__popcll(__ballot(key[r] >= (kth | ((unsigned)d << bit))));
+        kth |= (unsigned)(n[3] >= k ? 3 : n[2] >= k ? 2 : n[1] >= k ? 1 : 0) << bit;
+    }
+    int need = k;                                     // chunks to take among those at the k-th score
+#pragma unroll
+    for (int r = 0; r < R; ++r) need -= (int)__popcll(__ballot(key[r] > kth));
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool in = r * 64 + lane < nk;
+        const unsigned long long eq = __ballot(in && key[r] == kth);
+        const bool take = key[r] > kth || (in && key[r] == kth && (int)__popcll(eq & ((1ull << lane) - 1ull)) < need);
+        need -= (int)__popcll(eq);
+        if (in && r % nwave == wave) fsel[r * 64 + lane] = take;
+    }
+}
+
+// The first `want` free slots in the order of their keys (not negative; equal keys by id) into freelist, by
+// one wavefront: slots freed at the same step share a key, so each round takes all slots of the
+// smallest key left, in id order.  want: at most the free slots.
+template <int R>
+__device__ inline void first_slots_wave(const int *skey, int ns, int want, int *freelist)
+{
+    const int lane = threadIdx.x & 63;
+    int key[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int v = r * 64 + lane < ns ? skey[r * 64 + lane] : -1;
+        key[r] = v < 0 ? INT32_MAX : v;
+    }
+    for (int n = 0; n < want;) {
+        int m = key[0];
+#pragma unroll
+        for (int r = 1; r < R; ++r) m = min(m, key[r]);
+        // minimum of each row of 16 lanes, then of the four rows
+        m = min(m, __builtin_amdgcn_update_dpp(0, m, 0xB1, 0xF, 0xF, false));
+        m = min(m, __builtin_amdgcn_update_dpp(0, m, 0x4E, 0xF, 0xF, false));
+        m = min(m, __builtin_amdgcn_update_dpp(0, m, 0x141, 0xF, 0xF, false));
+        m = min(m, __builtin_amdgcn_update_dpp(0, m, 0x140, 0xF, 0xF, false));
+        m = min(min(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
+                min(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
+        if (m == INT32_MAX) break;                    // no free slot left
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const unsigned long long eq = __ballot(key[r] == m);
+            if (key[r] == m) {
+                const int at = n + (int)__popcll(eq & ((1ull << lane) - 1ull));
+                if (at < want) freelist[at] = r * 64 + lane;
+                key[r] = INT32_MAX;
+            }
+            n += (int)__popcll(eq);
+        }
+    }
+}
 
 // Per sequence b (state staged in shared memory, written back at the end).  Chunks (nchk) are
 // the selection's candidates; segments (nc) are the unit of masses, residency, slots and
@@ -829,23 +886,32 @@ __device__ inline void select_seq(const Geometry &g, const StepBuffers &s, float
             if (c >= 0 && c < nk) fsel[c] = 1;
         }
     } else {
-        // rank of every chunk among all (the number of larger keys): P adjacent lanes per chunk
-        // each compare it with a contiguous share of the chunks (independent shared-memory
-        // reads, unrolled), then add their counts across the P lanes
-        int P = 1;
-        while (P < 32 && 2 * P * nk <= nthr) P *= 2;
-        const int span = (nk + P - 1) / P;
-        for (int c0 = 0; c0 < nk * P; c0 += nthr) {
-            const int w = c0 + tid, c = w / P, part = w - c * P;
-            int cnt = 0;
-            if (c < nk) {
-                const unsigned long long kc = ckey[c];
-                const int ja = part * span, jb = min(nk, ja + span);
+        // Counting takes nk^2 comparisons over the work-group, the search 48 nk / 64 in one wavefront: on
+        // 235 chunks 4.2 against 3.0 us with 256 threads, 2.5 against 2.6 with 1024; on 32 chunks 0.7
+        // against 2.0; on 703 chunks the search takes 6.7 us.
+        if (nk > 128 && nk <= 256 && nthr <= 256)
+            top_k_wave<4>(ckey, nk, k, fsel);
+        else if (nk > 256 && nk <= 768)
+            top_k_wave<12>(ckey, nk, k, fsel);
+        else {
+            // rank of every chunk among all (the number of larger keys): P adjacent lanes per chunk
+            // each compare it with a contiguous share of the chunks (independent shared-memory
+            // reads, unrolled), then add their counts across the P lanes
+            int P = 1;
+            while (P < 32 && 2 * P * nk <= nthr) P *= 2;
+            const int span = (nk + P - 1) / P;
+            for (int c0 = 0; c0 < nk * P; c0 += nthr) {
+                const int w = c0 + tid, c = w / P, part = w - c * P;
+                int cnt = 0;
+                if (c < nk) {
+                    const unsigned long long kc = ckey[c];
+                    const int ja = part * span, jb = min(nk, ja + span);
 #pragma unroll 8
-                for (int j = ja; j < jb; ++j) cnt += ckey[j] > kc;
+                    for (int j = ja; j < jb; ++j) cnt += ckey[j] > kc;
+                }
+                for (int o = 1; o < P; o <<= 1) cnt += __shfl_xor(cnt, o);
+                if (c < nk && part == 0) fsel[c] = cnt < k;
             }
-            for (int o = 1; o < P; o <<= 1) cnt += __shfl_xor(cnt, o);
-            if (c < nk && part == 0) fsel[c] = cnt < k;
         }
     }
     lds_barrier();
@@ -976,7 +1042,15 @@ __device__ inline void select_seq(const Geometry &g, const StepBuffers &s, float
         if ((tid & 63) == 0 && bal) atomicAdd(&nfree, __popcll(bal));
     }
     lds_barrier();
-    {
+    // the first `want` of them in that order (none in a step that recalls nothing)
+    const int want = min(nnew, min(nfree, g.knew));
+    if (want > 0 && ns <= 256) {
+        if (tid < 64) first_slots_wave<4>(skey, ns, want, freelist);
+        lds_barrier();
+    } else if (want > 0 && ns <= 768) {
+        if (tid < 64) first_slots_wave<12>(skey, ns, want, freelist);
+        lds_barrier();
+    } else if (want > 0) {
         // every free slot counts the free slots ordered before it; the comparisons of one slot are
         // split over `split` threads that add their counts (integer sums: any order)
         const int split = max(1, nthr / max(ns, 1)), span_j = (ns + split - 1) / split;
@@ -989,11 +1063,11 @@ __device__ inline void select_seq(const Geometry &g, const StepBuffers &s, float
             for (int j = part * span_j, je = min(ns, (part + 1) * span_j); j < je; ++j) r += fkey[j] < ki;
             if (r) atomicAdd(&frank[i], r);
         }
+        lds_barrier();
+        for (int i = tid; i < ns; i += nthr)
+            if (skey[i] >= 0) freelist[frank[i]] = i;   // the ranks of the free slots are 0 .. nfree-1, each once
+        lds_barrier();
     }
-    lds_barrier();
-    for (int i = tid; i < ns; i += nthr)
-        if (skey[i] >= 0) freelist[frank[i]] = i;   // the ranks of the free slots are 0 .. nfree-1, each once
-    lds_barrier();
 
     // segments to recall take the free slots in that order (lowest id first)
     int32_t *nl = s.new_list + (size_t)b * g.knew * 2;
@@ -1609,6 +1683,34 @@ __device__ inline bool last_arrival(int32_t *cnt, int n, SelectShared &sh)
     return sh.last;
 }
 
+// The anchor merge and the selection inside the launch that runs the anchor tiles: the last tile of an
+// anchor head to end merges the head's chunk masses, and the last head of a sequence to be merged
+// runs the sequence's selection (sel.s: the lists it writes; `smem`: the work-group's shared memory).
+// A small cache's step is a chain of launches of 5 to 15 us, each mostly latency; this takes two of them
+// out, and beside static tiles the chain is partly hidden.  Whole steps, with the shorter merge and
+// top-k: 36 layers, 2 KV-heads, 7756 rows, next-step 88.2 -> 70 us (first launch 28 + 10.6 + 13.7 -> 34.6);
+// one layer, 8 KV-heads, 1064 rows, same-step 34.5 -> 30.7 us.
+template <int G>
+__device__ inline void select_after_tile(const Geometry &g, const SelectArgs &sel, int ai, int b, char *smem)
+{
+    SelectShared &sh = *(SelectShared *)smem;
+    __syncthreads();   // the tile's shared memory is free
+    if (!last_arrival(sel.s.arrive_head + (size_t)b * g.nA + ai, g.n_tiles_a, sh)) return;
+    double *dyn = (double *)(smem + SEL_SHARED_OFF);
+    anchor_mass_head<G, true>(g, sel.s, ai, b, dyn, *(MassSmem<G> *)(smem + sizeof(SelectShared)));
+    if (last_arrival(sel.s.arrive + b, g.nA, sh)) select_seq(g, sel.s, sel.scores, sel.ovr, sel.selected, b, dyn, sh);
+}
+
+// SEL: the merge and the selection in the same launch (see launch_anchor).
+template <int G, bool SEL>
+__global__ __launch_bounds__(NT, G <= 4 ? 4 : 2) void anchor_attn_kernel(Geometry g, Tiers t, StepBuffers s,
+                                                                         const uint16_t *__restrict__ q, SelectArgs sel)
+{
+    __shared__ AnchorSmem<G> sm;
+    anchor_tile<G, SEL>(g, t, s, q, blockIdx.x, blockIdx.y, blockIdx.z, sm);
+    if constexpr (SEL) select_after_tile<G>(g, sel, blockIdx.y, blockIdx.z, (char *)&sm);
+}
+
 // Fixed heads, tidal kept rows and tidal complements already in their slots: static tiles
 // first (unless the attention launch ran them), then the items of one list (list_item).  The
 // work-groups loop over those tiles with the grid's stride, so the launch holds about as many
@@ -1637,7 +1739,7 @@ __global__ __launch_bounds__(NT, REC ? (RPLK == RPL_S ? 2 : 1) : (G <= 4 ? 4 : G
         char *base = (char *)&sm;
         SelectShared &sh = *(SelectShared *)base;
         static_assert(sizeof(SelectShared) + sizeof(MassSmem<G>) <= SEL_SHARED_OFF, "counters before the arrays");
-        anchor_mass_head<G>(g, sel.s, ai, b, (double *)(base + SEL_SHARED_OFF), *(MassSmem<G> *)(base + sizeof(SelectShared)));
+        anchor_mass_head<G, false>(g, sel.s, ai, b, (double *)(base + SEL_SHARED_OFF), *(MassSmem<G> *)(base + sizeof(SelectShared)));
         if (last_arrival(sel.s.arrive + b, g.nA, sh))
             select_seq(g, sel.s, sel.scores, sel.ovr, sel.selected, b, (double *)(base + SEL_SHARED_OFF), sh);
         return;
@@ -1676,9 +1778,9 @@ __global__ __launch_bounds__(NT, REC ? (RPLK == RPL_S ? 2 : 1) : (G <= 4 ? 4 : G
 // in one launch, interleaved along the grid: the anchor tiles' arithmetic (fp64 logits)
 // overlaps the static tiles' streaming.  Used with next-step timing, where the static tiles need
 // not wait for this step's selection.
-template <int G>
+template <int G, bool SEL>
 __global__ __launch_bounds__(NT, G <= 4 ? 4 : 2) void attention_kernel(Geometry g, Tiers t, StepBuffers s,
-                                                                       const uint16_t *__restrict__ q)
+                                                                       const uint16_t *__restrict__ q, SelectArgs sel)
 {
     union Smem {
         AnchorSmem<G> a;
@@ -1693,13 +1795,17 @@ __global__ __launch_bounds__(NT, G <= 4 ? 4 : 2) void attention_kernel(Geometry 
     // (measured: 98.3 -> 96.2-97.1 us with the selection pinned; spread over the whole grid, or
     // over its first 70-85 %, ends later).
     const long long na = (long long)g.n_tiles_a * g.nA * g.B;
-    const long long n = na + (long long)g.n_static * g.B, m = std::max(n / 2, na);
+    // With SEL the anchor tiles come first: the merge and the selection that follow them are the
+    // launch's longest chain, and they run beside the static tiles.
+    const long long n = na + (long long)g.n_static * g.B, m = SEL ? na : std::max(n / 2, na);
     const long long p = blockIdx.x, a0 = p < m ? p * na / m : na, a1 = p < m ? (p + 1) * na / m : na;
     if (a1 > a0) {
         // anchors before this position: a0, so this is anchor tile a0
         const int tile = (int)(a0 % g.n_tiles_a);
         const long long rest = a0 / g.n_tiles_a;
-        anchor_tile<G>(g, t, s, q, tile, (int)(rest % g.nA), (int)(rest / g.nA), sm.a);
+        const int ai = (int)(rest % g.nA), b = (int)(rest / g.nA);
+        anchor_tile<G, SEL>(g, t, s, q, tile, ai, b, sm.a);
+        if constexpr (SEL) select_after_tile<G>(g, sel, ai, b, (char *)&sm);
     } else {
         const long long i = p - a0;   // static tiles before this position
         static_tile<G>(g, t, s, q, (int)(i % g.n_static), (int)(i / g.n_static), sm.st);
@@ -1948,11 +2054,12 @@ hipError_t dispatch_g(int G, A... args)
 template <int G>
 struct AnchorL {
     static hipError_t run(const Geometry &g, const Tiers &t, const StepBuffers &s, const uint16_t *q, hipStream_t st,
-                          hipEvent_t e0, hipEvent_t e1)
+                          hipEvent_t e0, hipEvent_t e1, const SelectArgs *selp)
     {
         if (g.nA == 0 || g.n_tiles_a == 0) return record_pair(e0, e1, st);
-        hipExtLaunchKernelGGL(anchor_attn_kernel<G>, dim3(g.n_tiles_a, g.nA, g.B), dim3(NT), 0, st, e0, e1, 0, g, t,
-                              s, q);
+        auto k = selp ? anchor_attn_kernel<G, true> : anchor_attn_kernel<G, false>;
+        hipExtLaunchKernelGGL(k, dim3(g.n_tiles_a, g.nA, g.B), dim3(NT), 0, st, e0, e1, 0, g, t, s, q,
+                              selp ? *selp : SelectArgs{});
         return hipGetLastError();
     }
 };
@@ -2019,23 +2126,38 @@ struct TidalFixedL {
         return hipGetLastError();
     }
 };
+// Whether `room` bytes after the counters hold the mass merge and the selection.
+template <int G>
+bool select_fits(const Geometry &g, size_t room)
+{
+    return g.nA > 0 && g.nc > 0 && select_shared_bytes(g) <= room && (size_t)G * g.n_tiles_a * sizeof(double) <= room;
+}
 template <int G>
 struct TidalSelectFits {
-    static bool run(const Geometry &g)
+    static hipError_t run(const Geometry &g, bool &fits)
     {
-        const size_t room = sizeof(SubsetSmem<G, RPL_S>) - SEL_SHARED_OFF;
-        return g.nA > 0 && g.nc > 0 && select_shared_bytes(g) <= room && (size_t)G * g.n_tiles_a * sizeof(double) <= room;
+        fits = select_fits<G>(g, sizeof(SubsetSmem<G, RPL_S>) - SEL_SHARED_OFF);
+        return hipSuccess;
+    }
+};
+template <int G>
+struct AnchorSelectFits {
+    static hipError_t run(const Geometry &g, bool &fits)
+    {
+        fits = select_fits<G>(g, sizeof(AnchorSmem<G>) - SEL_SHARED_OFF);
+        return hipSuccess;
     }
 };
 template <int G>
 struct AttentionL {
     static hipError_t run(const Geometry &g, const Tiers &t, const StepBuffers &s, const uint16_t *q, hipStream_t st,
-                          hipEvent_t e0, hipEvent_t e1)
+                          hipEvent_t e0, hipEvent_t e1, const SelectArgs *selp)
     {
         const long long n = (long long)g.n_tiles_a * g.nA * g.B + (long long)g.n_static * g.B;
         if (n == 0) return record_pair(e0, e1, st);
         if (n > INT32_MAX) return hipErrorInvalidValue;
-        hipExtLaunchKernelGGL(attention_kernel<G>, dim3((unsigned)n), dim3(NT), 0, st, e0, e1, 0, g, t, s, q);
+        auto k = selp ? attention_kernel<G, true> : attention_kernel<G, false>;
+        hipExtLaunchKernelGGL(k, dim3((unsigned)n), dim3(NT), 0, st, e0, e1, 0, g, t, s, q, selp ? *selp : SelectArgs{});
         return hipGetLastError();
     }
 };
@@ -2067,9 +2189,10 @@ struct CombineL {
 }  // namespace
 
 hipError_t launch_anchor(const Geometry &g, const Tiers &t, const StepBuffers &s, const uint16_t *q, hipStream_t st,
-                         hipEvent_t e0, hipEvent_t e1)
+                         hipEvent_t e0, hipEvent_t e1, const SelectArgs *sel)
 {
-    return dispatch_g<AnchorL>(g.G, g, t, s, q, st, e0, e1);
+    if (sel && (!sel->s.arrive || !anchor_select_fits(g))) return hipErrorInvalidValue;
+    return dispatch_g<AnchorL>(g.G, g, t, s, q, st, e0, e1, sel);
 }
 
 hipError_t launch_anchor_mass(const Geometry &g, const StepBuffers &s, hipStream_t st)
@@ -2095,21 +2218,21 @@ hipError_t launch_tidal_fixed(const Geometry &g, const Tiers &t, const StepBuffe
 
 bool tidal_select_fits(const Geometry &g)
 {
-    switch (g.G) {
-    case 1: return TidalSelectFits<1>::run(g);
-    case 2: return TidalSelectFits<2>::run(g);
-    case 3: return TidalSelectFits<3>::run(g);
-    case 4: return TidalSelectFits<4>::run(g);
-    case 6: return TidalSelectFits<6>::run(g);
-    case 8: return TidalSelectFits<8>::run(g);
-    default: return false;
-    }
+    bool fits = false;
+    return dispatch_g<TidalSelectFits, const Geometry &, bool &>(g.G, g, fits) == hipSuccess && fits;
+}
+
+bool anchor_select_fits(const Geometry &g)
+{
+    bool fits = false;
+    return dispatch_g<AnchorSelectFits, const Geometry &, bool &>(g.G, g, fits) == hipSuccess && fits;
 }
 
 hipError_t launch_attention(const Geometry &g, const Tiers &t, const StepBuffers &s, const uint16_t *q, hipStream_t st,
-                            hipEvent_t e0, hipEvent_t e1)
+                            hipEvent_t e0, hipEvent_t e1, const SelectArgs *sel)
 {
-    return dispatch_g<AttentionL>(g.G, g, t, s, q, st, e0, e1);
+    if (sel && (!sel->s.arrive || !anchor_select_fits(g))) return hipErrorInvalidValue;
+    return dispatch_g<AttentionL>(g.G, g, t, s, q, st, e0, e1, sel);
 }
 
 hipError_t launch_recall(const Geometry &g, const Tiers &t, const StepBuffers &s, hipStream_t st)
