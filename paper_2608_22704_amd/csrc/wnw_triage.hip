@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <numeric>
 #include <type_traits>
 #include <vector>
@@ -494,48 +495,151 @@ __global__ __launch_bounds__(NT, 4) void voice_hits_kernel(int L, int Hq, int Hk
     }
 }
 
-// One work-group of KS_THREADS per (answer token, KV-head) row of T_a gradient vectors: sixteen
-// threads per position (eight floats each), four positions per thread in flight; the
-// per-position norms are summed in double in a fixed order.
-constexpr int KS_THREADS = 1024, KS_SLOTS = KS_THREADS / 16, KS_UNROLL = 4;
+// Rows of T_a gradient vectors, one per (answer token, KV-head); `parts` work-groups of KS_THREADS per row,
+// each with `len` positions of it (a multiple of the round).  Sixteen lanes per position (eight floats
+// each), KS_UNROLL positions per lane and round, the next round's loads in flight while this one is
+// summed: the sixteen lanes sum their squares so that lane u of the row ends with round u's position,
+// and one square root in double serves the round.  Norms are summed in double in a fixed order.
+//
+// What bounds it: HBM, once enough compute units stream; one alone takes about 30 GB/s whatever is in
+// flight, so with few rows a row is split.  The parts' sums meet in a slot of the library (KsSlot), and
+// the last work-group of a row to arrive adds them in order.  72 rows of 7500 positions (276 MB):
+// 134 us with one work-group per row, 54.5 us split (5.1 TB/s); 8 rows of 15000 214 -> 19.6 us.
+constexpr int KS_THREADS = 512, KS_SLOTS = KS_THREADS / 16, KS_UNROLL = 4;
 typedef float f4v __attribute__((ext_vector_type(4)));
-__global__ __launch_bounds__(KS_THREADS) void key_sens_kernel(int Ta, const float *__restrict__ grad,
-                                                             float *__restrict__ sens)
+
+template <int CTRL>
+__device__ inline float row_perm(float v)
 {
-    const size_t row = blockIdx.x;
-    const f4v *G4 = (const f4v *)(grad + row * (size_t)Ta * D);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+constexpr int KS_STEP = KS_SLOTS * KS_UNROLL;   // positions of a work-group's round
+constexpr int KS_PARTS = 768, KS_ROWS = 256;   // most parts of a split launch, most rows
+struct KsSlot {
+    double part[KS_PARTS];
+    int arrived[KS_ROWS];                       // zero between launches
+};
+constexpr int KS_NSLOT = 8;
+static __device__ KsSlot ks_slots[KS_NSLOT];
+
+__global__ __launch_bounds__(KS_THREADS) void key_sens_kernel(int Ta, int parts, int len, int slot_id,
+                                                             const float *__restrict__ grad, float *__restrict__ sens)
+{
+    static_assert(KS_UNROLL == 4, "the sums below hand lane u the position of round u");
+    constexpr int STEP = KS_STEP;
+    const size_t row = blockIdx.x / (unsigned)parts;
+    const int pt = (int)(blockIdx.x - row * parts), end = min(Ta, (pt + 1) * len);
     const int tid = threadIdx.x, l16 = tid & 15, slot = tid >> 4;
-    double acc = 0.0;
-    for (int t0 = slot; t0 < Ta; t0 += KS_SLOTS * KS_UNROLL) {
+    const f4v *G4 = (const f4v *)(grad + row * (size_t)Ta * D) + 2 * l16;
+    struct Round {
         f4v a[KS_UNROLL], b[KS_UNROLL];
+    };
+    // positions t0 + slot + 64 u; past the last one that comes again (not summed)
+    auto load = [&](Round &r, int t0) {
 #pragma unroll
         for (int u = 0; u < KS_UNROLL; ++u) {
-            const int tau = t0 + u * KS_SLOTS;
-            if (tau < Ta) {
-                a[u] = __builtin_nontemporal_load(&G4[(size_t)tau * (D / 4) + 2 * l16]);
-                b[u] = __builtin_nontemporal_load(&G4[(size_t)tau * (D / 4) + 2 * l16 + 1]);
-            } else {
-                a[u] = b[u] = f4v{0.f, 0.f, 0.f, 0.f};
-            }
+            const f4v *p = G4 + (size_t)min(t0 + slot + u * KS_SLOTS, end - 1) * (D / 4);
+            r.a[u] = __builtin_nontemporal_load(p);
+            r.b[u] = __builtin_nontemporal_load(p + 1);
         }
+    };
+    double acc = 0.0;   // lanes 0..3 of a row of sixteen: positions of round 0..3
+    auto add = [&](const Round &r, int t0) {
+        float s2[KS_UNROLL];
 #pragma unroll
         for (int u = 0; u < KS_UNROLL; ++u) {
-            float s2 = a[u].x * a[u].x + a[u].y * a[u].y + a[u].z * a[u].z + a[u].w * a[u].w + b[u].x * b[u].x +
-                       b[u].y * b[u].y + b[u].z * b[u].z + b[u].w * b[u].w;
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) s2 += __shfl_xor(s2, o);
-            if (l16 == 0 && t0 + u * KS_SLOTS < Ta) acc += sqrt((double)s2);
+            const f4v a = r.a[u], b = r.b[u];
+            s2[u] = (a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w) + (b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w);
         }
+        const bool odd = l16 & 1, up = l16 & 2;
+        // with the neighbour (lane ^ 1), then with lane ^ 2: one position per lane of a quad
+        const float p01 = (odd ? s2[1] : s2[0]) + row_perm<0xB1>(odd ? s2[0] : s2[1]);
+        const float p23 = (odd ? s2[3] : s2[2]) + row_perm<0xB1>(odd ? s2[2] : s2[3]);
+        float q = (up ? p23 : p01) + row_perm<0x4E>(up ? p01 : p23);
+        q += row_perm<0x124>(q);   // the four quads of the row: rotations by four lanes, then by eight
+        q += row_perm<0x128>(q);
+        if (l16 < KS_UNROLL && t0 + slot + l16 * KS_SLOTS < end) acc += sqrt((double)q);
+    };
+    Round r0, r1;
+    load(r0, pt * len);
+    for (int t0 = pt * len; t0 < end; t0 += 2 * STEP) {
+        load(r1, t0 + STEP);
+        add(r0, t0);
+        load(r0, t0 + 2 * STEP);
+        add(r1, t0 + STEP);
     }
-    __shared__ double red[KS_SLOTS];
-    if (l16 == 0) red[slot] = acc;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) acc += __shfl_xor(acc, o);
+    __shared__ double red[KS_THREADS / 64];
+    if ((tid & 63) == 0) red[tid >> 6] = acc;
     __syncthreads();
     if (tid == 0) {
         double s = 0.0;
-        for (int i = 0; i < KS_SLOTS; ++i) s += red[i];
+        for (int i = 0; i < KS_THREADS / 64; ++i) s += red[i];
+        if (parts > 1) {
+            // agent-scope stores and loads around an agent-scope count: coherent across the dies' caches
+            KsSlot &sl = ks_slots[slot_id];
+            double *p = sl.part + row * parts;
+            __hip_atomic_store(p + pt, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (atomicAdd(&sl.arrived[row], 1) != parts - 1) return;
+            atomicExch(&sl.arrived[row], 0);
+            s = 0.0;
+            for (int i = 0; i < parts; ++i) s += __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         sens[row] = (float)(s / Ta);
     }
 }
+
+// Slots of split launches, per device: a launch takes the next slot and waits on the device for the
+// slot's previous launch (an event), whatever stream or thread that came from.
+struct KsSlots {
+    std::mutex mu;
+    hipEvent_t done[KS_NSLOT] = {};
+    unsigned next = 0;
+};
+constexpr int KS_MAX_DEVICES = 64;
+KsSlots ks_host[KS_MAX_DEVICES];
+
+hipError_t launch_key_sens(int64_t n, int Ta, const float *grad, float *sens, hipStream_t st)
+{
+    int dev = 0, n_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    // Fewer rows than three quarters of the compute units: parts for three work-groups a unit, of four rounds
+    // or more (240 rows unsplit stream at 5.9 TB/s; on 600 positions the slot's event costs more than the
+    // split gives, 13.9 against 11.5 us)
+    int parts = 1, len = Ta;
+    if (n * 4 < n_cu * 3 && n <= KS_ROWS && Ta >= 8 * KS_STEP && dev < KS_MAX_DEVICES) {
+        const int64_t want = std::min<int64_t>(3 * n_cu, KS_PARTS) / n;
+        len = (int)std::max<int64_t>(4 * KS_STEP, ((Ta + want - 1) / want + KS_STEP - 1) / KS_STEP * KS_STEP);
+        parts = (int)((Ta + (int64_t)len - 1) / len);
+        // a captured launch may be replayed beside others: it keeps one work-group per row, and no slot
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (parts > 1 && (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) {
+            (void)hipGetLastError();
+            parts = 1;
+        }
+    }
+    if (parts == 1) {
+        hipLaunchKernelGGL(key_sens_kernel, dim3((unsigned)n), dim3(KS_THREADS), 0, st, Ta, 1, Ta, 0, grad, sens);
+        return hipGetLastError();
+    }
+    KsSlots &h = ks_host[dev];
+    std::lock_guard<std::mutex> lk(h.mu);
+    const int i = (int)(h.next++ % KS_NSLOT);
+    if (h.done[i])
+        e = hipStreamWaitEvent(st, h.done[i], 0);
+    else
+        e = hipEventCreateWithFlags(&h.done[i], hipEventDisableTiming | hipEventDisableSystemFence);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(key_sens_kernel, dim3((unsigned)(n * parts)), dim3(KS_THREADS), 0, st, Ta, parts, len, i, grad, sens);
+    e = hipGetLastError();
+    return e == hipSuccess ? hipEventRecord(h.done[i], st) : e;
+}
+
 
 // Rows per work-group of the screen: as many of 128, 64, 32 as there are and as leave every compute
 // unit a work-group; fewer rows mean more shares of the keys.
@@ -615,9 +719,7 @@ wnw_status wnw_key_sensitivity(int32_t layers, int32_t kv_heads, int32_t audio_l
     if (n == 0) return WNW_OK;
     if (n > INT32_MAX) return triage_fail(WNW_ERR_UNSUPPORTED, "too many rows");
     if (!grad_dev || !sens_dev) return triage_fail(WNW_ERR_INVALID, "NULL pointer");
-    hipLaunchKernelGGL(key_sens_kernel, dim3((unsigned)n), dim3(KS_THREADS), 0, (hipStream_t)hip_stream, audio_len,
-                       grad_dev, sens_dev);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_key_sens(n, audio_len, grad_dev, sens_dev, (hipStream_t)hip_stream);
     return e == hipSuccess ? WNW_OK : triage_fail(WNW_ERR_HIP, hipGetErrorString(e));
 }
 
