@@ -7,8 +7,8 @@
 // and to text rows 0..t.  Per KV-head this is S = Q K^T with Q the g * T_t text query rows and K
 // the T_a + T_t key rows, a dense contraction, so both passes run on the bf16 matrix cores (fp32
 // accumulation):
-//   pass 1 (prefill_rowstats_kernel): per query row, 64 minus the log-sum-exp of its logits over its
-//           causal key set (base 2);
+//   pass 1 (prefill_rowstats_kernel): per query row, STAT_BIAS minus the log-sum-exp of its logits over
+//           its causal key set (base 2);
 //   pass 2 (prefill_colsum_kernel): per audio key, the sum over all query rows of
 //           exp(s - lse).  Audio keys are visible to every text row, so pass 2 needs no mask.
 // The streamed operand of either pass (K rows, then query rows) goes straight from global to shared
@@ -39,6 +39,9 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float C2 = 0.08838834764831845f * LOG2E;   // logit scale 1 / sqrt(128), base 2
+// Added to every exponent of pass 2: 32 lets terms down to 2^-158 count, for sums that fp32 holds from 2^-126
+// up, and costs half the rounding of 64 (error against 64 bits 8.2e-7 with 64).
+constexpr float STAT_BIAS = 32.f;
 constexpr int PT = 64;                                // rows per tile in shared memory
 constexpr int PBUF = 3;                               // tiles in shared memory, two of them in flight
 constexpr int PPF = PT * (D / 8) / NT;                // 16-byte pieces per lane and tile
@@ -212,7 +215,7 @@ __global__ __launch_bounds__(NT, NB == 2 ? 2 : 3) void prefill_rowstats_kernel(G
         const float m2 = __shfl_xor(m, 32), s2 = __shfl_xor(s, 32);
         merge_ms(m, s, m2, s2);
         const int r = rw + n * 32;
-        if (half == 0 && r < R) stat[qbase + r] = (64.f - m) - log2f(s);
+        if (half == 0 && r < R) stat[qbase + r] = (STAT_BIAS - m) - log2f(s);
     }
 }
 
@@ -268,9 +271,9 @@ __global__ __launch_bounds__(NT, 3) void prefill_colsum_kernel(Geometry g, const
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) fo[kk] = (unsigned)(col * (D * 2) + ((4 * kk + grp) ^ col) * 16);
     float acc[KB] = {};
-    // Terms are taken as 2^(x - lse + 64), with 64 - lse from pass 1, and the sum scaled by 2^-64 at the
-    // end, so that terms below 2^-126 still count without the exponential's range fix-up (terms are at
-    // most 1 and sums of at most R of them stay far below the fp32 range).
+    // Terms are taken as 2^(x - lse + STAT_BIAS), with STAT_BIAS - lse from pass 1, and the sum scaled back
+    // at the end, so that terms below 2^-126 still count without the exponential's range fix-up (terms
+    // are at most 1 and sums of at most R of them stay far below the fp32 range).
     const int nt = (R + PT - 1) / PT;
 #pragma unroll
     for (int i = 0; i < PBUF - 1; ++i) issue(i, i);
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(NT, 3) void prefill_colsum_kernel(Geometry g, const
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
             const int key = kw + kb * 16 + col;
-            if (key < g.Ta) p[(size_t)hd * g.Ta + key] = ldexpf(acc[kb], -64);
+            if (key < g.Ta) p[(size_t)hd * g.Ta + key] = ldexpf(acc[kb], -(int)STAT_BIAS);
         }
 }
 
