@@ -17,7 +17,7 @@
 //
 // What bounds it: per logit and pass, an FMA, an exponential and an addition next to 256 flop on the
 // matrix cores, and the chip's power: on 240 KV-heads, 15000 keys and 2048 rows the clock falls to
-// 1.6-1.7 GHz, with the matrix cores busy 57-63 % of the cycles and the vector unit 70 %.  There both
+// 1.6-1.7 GHz, with the matrix cores busy 50-57 % of the cycles and the vector unit 65-75 %.  There both
 // passes took 4.06-4.4 ms staged through registers with 16 x 16 products in pass 1, and take 3.45-3.6 ms
 // now (3.8 TFLOP executed: 1.1 PFLOP/s, what a bf16 matrix product of 8192 reaches on the card); on 72
 // KV-heads, 3607 keys and 1176 rows 205-215 us, now 178-187 us.  A loop that takes one product's terms
