@@ -32,7 +32,6 @@ PEAK_HBM_GBPS = 8000.0
 TIMED_FROM = 16                # first clip step of the timed region (the warm-up runs the steps before it)
 PEAK_BF16_TFLOPS = 2500.0      # dense bf16 MFMA
 PEAK_LINK_GBPS = 64.0          # PCIe 5.0 x16, one direction
-PEAK_FP64_TFLOPS = 78.6        # fp64, matrix cores (the vector rate is the same)
 
 
 def log(msg):
@@ -508,8 +507,8 @@ def prefill_bench(W, torch, w, kd, vd, roles, reps=5):
 
 def triage_bench(W, torch, w, kd, n_tok=64, reps=5):
     """Head triage arithmetic at the workload's shapes (one calibration sample): voice-score hits
-    of n_tok answer tokens (fp64 dot products over every audio key: 2 d flops per token, q-head
-    and audio key), and the key sensitivity of one answer token (a read of its fp32 key gradients:
+    of n_tok answer tokens (dot products over every audio key, 2 d flops per token, q-head and audio
+    key, screened in bf16 and decided in fp64), and the key sensitivity of one answer token (a read of its fp32 key gradients:
     L * H_kv * T_a * d * 4 bytes).  Synthetic inputs; calibration itself is offline."""
     L, Hq, H, D, Ta, T = w.layers, w.q_heads, w.kv_heads, w.head_dim, w.audio_len, w.total_len
     g = torch.Generator(device="cuda").manual_seed(5)
@@ -541,7 +540,7 @@ def triage_bench(W, torch, w, kd, n_tok=64, reps=5):
     del grad
     log(f"[bench] triage: voice hits {vh:.3f} ms, key sensitivity {ks:.3f} ms")
     return {"voice_hits_ms": vh, "voice_hits_tokens": n_tok, "voice_hits_tflops": flop / (vh * 1e-3) / 1e12,
-            "voice_hits_frac": flop / (vh * 1e-3) / 1e12 / PEAK_FP64_TFLOPS, "voice_hits_bound": "fp64 mfma",
+            "voice_hits_frac": flop / (vh * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, "voice_hits_bound": "bf16 mfma (screen)",
             "key_sensitivity_ms": ks, "key_sensitivity_GBps": nbytes / (ks * 1e-3) / 1e9,
             "key_sensitivity_frac": nbytes / (ks * 1e-3) / 1e9 / PEAK_HBM_GBPS,
             "note": "offline calibration arithmetic on synthetic inputs; one sample, K = 4"}
