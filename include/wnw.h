@@ -381,7 +381,7 @@ wnw_status wnw_voice_hits(int32_t layers, int32_t q_heads, int32_t kv_heads, int
  * gradient at that position's key.
  *   grad_dev  device fp32 [n_tok][L][H_kv][audio_len][d]
  *   sens_dev  device fp32 [n_tok][L][H_kv], written
- * Enqueued on hip_stream. */
+ * Enqueued on hip_stream; depends on no other stream. */
 wnw_status wnw_key_sensitivity(int32_t layers, int32_t kv_heads, int32_t audio_len, int32_t n_tok, const float *grad_dev,
                                float *sens_dev, void *hip_stream);
 

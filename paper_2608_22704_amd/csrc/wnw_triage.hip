@@ -17,13 +17,13 @@
 #include "wnw.h"
 #include "wnw_internal.h"
 #include "wnw_lds.h"
+#include "wnw_slots.h"
 
 #include <float.h>
 #include <math.h>
 
 #include <algorithm>
 #include <cstring>
-#include <mutex>
 #include <numeric>
 #include <type_traits>
 #include <vector>
@@ -503,7 +503,8 @@ __global__ __launch_bounds__(NT, 4) void voice_hits_kernel(int L, int Hq, int Hk
 //
 // What bounds it: HBM, once enough compute units stream; one alone takes about 30 GB/s whatever is in
 // flight, so with few rows a row is split.  The parts' sums meet in a slot of the library (KsSlot), and
-// the last work-group of a row to arrive adds them in order.  72 rows of 7500 positions (276 MB):
+// the last work-group of a row to arrive adds them in order.  A launch takes a slot that its own stream used
+// last or whose last user has ended, never one to wait for; with none it is not split.  72 rows of 7500 positions (276 MB):
 // 134 us with one work-group per row, 54.5 us split (5.1 TB/s); 8 rows of 15000 214 -> 19.6 us.
 constexpr int KS_THREADS = 512, KS_SLOTS = KS_THREADS / 16, KS_UNROLL = 4;
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -592,15 +593,42 @@ __global__ __launch_bounds__(KS_THREADS) void key_sens_kernel(int Ta, int parts,
     }
 }
 
-// Slots of split launches, per device: a launch takes the next slot and waits on the device for the
-// slot's previous launch (an event), whatever stream or thread that came from.
-struct KsSlots {
-    std::mutex mu;
-    hipEvent_t done[KS_NSLOT] = {};
-    unsigned next = 0;
+// The runtime's calls of the slot pool.  Other threads may be capturing: queries and event creation are not
+// part of any capture, so this thread's calls are exempt from its check.
+struct HipSlotRT {
+    using Stream = hipStream_t;
+    using Event = hipEvent_t;
+    using Error = hipError_t;
+    struct Uncaptured {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        Uncaptured() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+        ~Uncaptured() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    };
+    // a failure that the caller goes round leaves no error behind for the next launch's check
+    static Error handled(Error e)
+    {
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
+    }
+    static bool ok(Error e) { return e == hipSuccess; }
+    static Error create(Event &ev)
+    {
+        Uncaptured u;
+        return handled(hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventDisableSystemFence));
+    }
+    static Error query(Event ev, bool &ended)
+    {
+        Uncaptured u;
+        const Error e = handled(hipEventQuery(ev));
+        ended = e == hipSuccess;
+        return e == hipErrorNotReady ? hipSuccess : e;
+    }
+    static Error wait(Stream st, Event ev) { return handled(hipStreamWaitEvent(st, ev, 0)); }
+    static Error record(Event ev, Stream st) { return hipEventRecord(ev, st); }
+    static bool shared_handle(Stream st) { return st == hipStreamPerThread; }
 };
 constexpr int KS_MAX_DEVICES = 64;
-KsSlots ks_host[KS_MAX_DEVICES];
+SlotPool<HipSlotRT, KS_NSLOT> ks_pool[KS_MAX_DEVICES];   // per device, for split launches
 
 hipError_t launch_key_sens(int64_t n, int Ta, const float *grad, float *sens, hipStream_t st)
 {
@@ -612,7 +640,10 @@ hipError_t launch_key_sens(int64_t n, int Ta, const float *grad, float *sens, hi
     // or more (240 rows unsplit stream at 5.9 TB/s; on 600 positions the slot's event costs more than the
     // split gives, 13.9 against 11.5 us)
     int parts = 1, len = Ta;
-    if (n * 4 < n_cu * 3 && n <= KS_ROWS && Ta >= 8 * KS_STEP && dev < KS_MAX_DEVICES) {
+    // (a stream of another device than the current one, where the slots' events belong: not split)
+    hipDevice_t sdev = dev;
+    if (st != nullptr && HipSlotRT::handled(hipStreamGetDevice(st, &sdev)) != hipSuccess) sdev = -1;
+    if (n * 4 < n_cu * 3 && n <= KS_ROWS && Ta >= 8 * KS_STEP && dev < KS_MAX_DEVICES && sdev == dev) {
         const int64_t want = std::min<int64_t>(3 * n_cu, KS_PARTS) / n;
         len = (int)std::max<int64_t>(4 * KS_STEP, ((Ta + want - 1) / want + KS_STEP - 1) / KS_STEP * KS_STEP);
         parts = (int)((Ta + (int64_t)len - 1) / len);
@@ -623,23 +654,13 @@ hipError_t launch_key_sens(int64_t n, int Ta, const float *grad, float *sens, hi
             parts = 1;
         }
     }
-    if (parts == 1) {
-        hipLaunchKernelGGL(key_sens_kernel, dim3((unsigned)n), dim3(KS_THREADS), 0, st, Ta, 1, Ta, 0, grad, sens);
+    auto launch = [&](int np, int nl, int slot) {
+        hipLaunchKernelGGL(key_sens_kernel, dim3((unsigned)(n * np)), dim3(KS_THREADS), 0, st, Ta, np, nl, slot, grad, sens);
         return hipGetLastError();
-    }
-    KsSlots &h = ks_host[dev];
-    std::lock_guard<std::mutex> lk(h.mu);
-    const int i = (int)(h.next++ % KS_NSLOT);
-    if (h.done[i])
-        e = hipStreamWaitEvent(st, h.done[i], 0);
-    else
-        e = hipEventCreateWithFlags(&h.done[i], hipEventDisableTiming | hipEventDisableSystemFence);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(key_sens_kernel, dim3((unsigned)(n * parts)), dim3(KS_THREADS), 0, st, Ta, parts, len, i, grad, sens);
-    e = hipGetLastError();
-    return e == hipSuccess ? hipEventRecord(h.done[i], st) : e;
+    };
+    if (parts > 1 && ks_pool[dev].run(st, e, [&](int slot) { return launch(parts, len, slot); })) return e;
+    return launch(1, Ta, 0);   // one work-group per row: no slot
 }
-
 
 // Rows per work-group of the screen: as many of 128, 64, 32 as there are and as leave every compute
 // unit a work-group; fewer rows mean more shares of the keys.

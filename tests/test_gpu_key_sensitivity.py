@@ -87,3 +87,88 @@ def test_split_rows_on_streams_and_threads_and_captured():
         graph.replay()
         torch.cuda.synchronize()
         assert float(((sens - want) / want).abs().max()) <= RTOL
+
+
+def test_split_rows_depend_on_no_other_stream():
+    """A stream is held back by a sleeping kernel with a call queued behind it; calls on another stream
+    end meanwhile."""
+    import time
+    import torch
+    from paper_2608_22704_amd import wnw as W
+    from tests.wnw_harness import log
+    log("[case] key sensitivity on one stream while another with a queued call is held back")
+    grad, want = _case(5, 1, 4, 3, 3000)
+    outs = [torch.full(grad.shape[:3], -1.0, device="cuda") for _ in range(25)]
+    W.wnw_key_sensitivity(grad, outs[0])
+    torch.cuda._sleep(1000)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    torch.cuda._sleep(1_000_000)
+    torch.cuda.synchronize()
+    per_ms = 1_000_000 / (1e3 * (time.perf_counter() - t0))   # what the sleeping kernel counts in a millisecond
+
+    def hold(st, ms):
+        awake = torch.cuda.Event()
+        with torch.cuda.stream(st):
+            torch.cuda._sleep(int(per_ms * ms))
+            awake.record()
+        return awake
+
+    # two streams may share a hardware queue, where one's work runs behind the other's whatever the library
+    # does: take one that does not
+    held, other = torch.cuda.Stream(), None
+    for st in [torch.cuda.Stream() for _ in range(6)]:
+        awake = hold(held, 100)
+        with torch.cuda.stream(st):
+            outs[0].fill_(-1.0)
+        st.synchronize()
+        free = not awake.query()
+        torch.cuda.synchronize()
+        if free:
+            other = st
+            break
+    if other is None:
+        pytest.skip("no stream with a hardware queue of its own")
+    awake = hold(held, 300)
+    W.wnw_key_sensitivity(grad, outs[0], held)
+    for o in outs[1:]:
+        W.wnw_key_sensitivity(grad, o, other)
+    other.synchronize()
+    asleep = not awake.query()
+    torch.cuda.synchronize()
+    assert asleep, "calls on one stream waited for another"
+    for o in outs:
+        assert float(((o - want) / want).abs().max()) <= RTOL
+
+
+def test_split_rows_while_another_thread_captures():
+    import torch
+    from paper_2608_22704_amd import wnw as W
+    from tests.wnw_harness import log
+    log("[case] key sensitivity, eager calls of a thread while another captures")
+    grad, want = _case(6, 1, 4, 3, 3000)
+    outs = [torch.full(grad.shape[:3], -1.0, device="cuda") for _ in range(5)]
+    st, failed = torch.cuda.Stream(), []
+    W.wnw_key_sensitivity(grad, outs[4], st)
+
+    def run():
+        try:
+            for o in outs[1:4]:
+                W.wnw_key_sensitivity(grad, o, st)
+        except Exception as e:   # reported by the main thread
+            failed.append(e)
+
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        W.wnw_key_sensitivity(grad, outs[0])
+        t = threading.Thread(target=run)
+        t.start()
+        t.join()
+        W.wnw_key_sensitivity(grad, outs[4])
+    assert not failed, failed
+    outs[4].fill_(-1.0)
+    graph.replay()
+    torch.cuda.synchronize()
+    for o in outs:
+        assert float(((o - want) / want).abs().max()) <= RTOL
