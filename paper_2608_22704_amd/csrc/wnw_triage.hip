@@ -504,8 +504,8 @@ __global__ __launch_bounds__(NT, 4) void voice_hits_kernel(int L, int Hq, int Hk
 // What bounds it: HBM, once enough compute units stream; one alone takes about 30 GB/s whatever is in
 // flight, so with few rows a row is split.  The parts' sums meet in a slot of the library (KsSlot), and
 // the last work-group of a row to arrive adds them in order.  A launch takes a slot that its own stream used
-// last or whose last user has ended, never one to wait for; with none it is not split.  72 rows of 7500 positions (276 MB):
-// 134 us with one work-group per row, 54.5 us split (5.1 TB/s); 8 rows of 15000 214 -> 19.6 us.
+// last or whose last user has ended, never one to wait for; with none it is not split.  72 rows of 7500
+// positions (276 MB): 134 us with one work-group per row, 54.5 us split (5.1 TB/s); 8 rows of 15000 214 -> 19.6 us.
 constexpr int KS_THREADS = 512, KS_SLOTS = KS_THREADS / 16, KS_UNROLL = 4;
 typedef float f4v __attribute__((ext_vector_type(4)));
 
@@ -524,6 +524,8 @@ struct KsSlot {
 constexpr int KS_NSLOT = 8;
 static __device__ KsSlot ks_slots[KS_NSLOT];
 
+// SPLIT: `parts` > 1.
+template <bool SPLIT>
 __global__ __launch_bounds__(KS_THREADS) void key_sens_kernel(int Ta, int parts, int len, int slot_id,
                                                              const float *__restrict__ grad, float *__restrict__ sens)
 {
@@ -563,12 +565,31 @@ __global__ __launch_bounds__(KS_THREADS) void key_sens_kernel(int Ta, int parts,
         if (l16 < KS_UNROLL && t0 + slot + l16 * KS_SLOTS < end) acc += sqrt((double)q);
     };
     Round r0, r1;
-    load(r0, pt * len);
-    for (int t0 = pt * len; t0 < end; t0 += 2 * STEP) {
-        load(r1, t0 + STEP);
-        add(r0, t0);
-        load(r0, t0 + 2 * STEP);
-        add(r1, t0 + STEP);
+    int t0 = pt * len;
+    load(r0, t0);
+    if constexpr (SPLIT) {
+        // The rounds past the last position load it again.  Without those loads 72 rows of 7500 take 62 us
+        // instead of 54.5; unsplit, with more rows than the chip holds at once, they cost: 600 rows of 300
+        // positions 24.7 us with them, 19.1 without.
+        for (; t0 < end; t0 += 2 * STEP) {
+            load(r1, t0 + STEP);
+            add(r0, t0);
+            load(r0, t0 + 2 * STEP);
+            add(r1, t0 + STEP);
+        }
+    } else {
+        for (; t0 + 2 * STEP < end; t0 += 2 * STEP) {
+            load(r1, t0 + STEP);
+            add(r0, t0);
+            load(r0, t0 + 2 * STEP);
+            add(r1, t0 + STEP);
+        }
+        if (t0 + STEP < end) {
+            load(r1, t0 + STEP);
+            add(r0, t0);
+            add(r1, t0 + STEP);
+        } else
+            add(r0, t0);
     }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) acc += __shfl_xor(acc, o);
@@ -578,7 +599,7 @@ __global__ __launch_bounds__(KS_THREADS) void key_sens_kernel(int Ta, int parts,
     if (tid == 0) {
         double s = 0.0;
         for (int i = 0; i < KS_THREADS / 64; ++i) s += red[i];
-        if (parts > 1) {
+        if constexpr (SPLIT) {
             // agent-scope stores and loads around an agent-scope count: coherent across the dies' caches
             KsSlot &sl = ks_slots[slot_id];
             double *p = sl.part + row * parts;
@@ -630,23 +651,37 @@ struct HipSlotRT {
 constexpr int KS_MAX_DEVICES = 64;
 SlotPool<HipSlotRT, KS_NSLOT> ks_pool[KS_MAX_DEVICES];   // per device, for split launches
 
+// Positions from which rows are split into `want` parts (0: never).  A split costs its slot 2 to 4 us.
+// Measured unsplit and split: at 5 or fewer parts 144 rows of 1024 21.8 and 23.1 us, of 1300 26.9 and 24.3; at 4
+// 191 rows of 2100 44.8 and 50.4, of 3000 62.8 and 53.6.  Few rows of few positions stream from the caches: 16
+// rows of 1300 11.2 and 12.6, of 1500 14.1 and 12.6; 36 rows of 1024 10.8 and 12.8, of 1300 15.4 and 13.0.  72 rows
+// of 1024 19.0 and 13.6; 240 rows unsplit stream at 5.6 TB/s.
+int64_t ks_split_from(int64_t n, int64_t want)
+{
+    if (want < 4) return 0;
+    if (want == 4) return 20 * KS_STEP;
+    if (want == 5) return 9 * KS_STEP;
+    return std::min<int64_t>(12 * KS_STEP, std::max<int64_t>(8 * KS_STEP, 45000 / n));
+}
+
 hipError_t launch_key_sens(int64_t n, int Ta, const float *grad, float *sens, hipStream_t st)
 {
-    int dev = 0, n_cu = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    // Fewer rows than three quarters of the compute units: parts for three work-groups a unit, of four rounds
-    // or more (240 rows unsplit stream at 5.9 TB/s; on 600 positions the slot's event costs more than the
-    // split gives, 13.9 against 11.5 us)
-    int parts = 1, len = Ta;
-    // (a stream of another device than the current one, where the slots' events belong: not split)
-    hipDevice_t sdev = dev;
-    if (st != nullptr && HipSlotRT::handled(hipStreamGetDevice(st, &sdev)) != hipSuccess) sdev = -1;
-    if (n * 4 < n_cu * 3 && n <= KS_ROWS && Ta >= 8 * KS_STEP && dev < KS_MAX_DEVICES && sdev == dev) {
-        const int64_t want = std::min<int64_t>(3 * n_cu, KS_PARTS) / n;
-        len = (int)std::max<int64_t>(4 * KS_STEP, ((Ta + want - 1) / want + KS_STEP - 1) / KS_STEP * KS_STEP);
-        parts = (int)((Ta + (int64_t)len - 1) / len);
+    int parts = 1, len = Ta, dev = 0;
+    hipError_t e = hipSuccess;
+    if (n <= KS_ROWS && Ta >= 8 * KS_STEP) {
+        // parts for three work-groups a unit, of four rounds or more; none for a stream of another device than
+        // the current one, where the slots' events belong
+        int n_cu = 0;
+        e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        hipDevice_t sdev = dev;
+        if (st != nullptr && HipSlotRT::handled(hipStreamGetDevice(st, &sdev)) != hipSuccess) sdev = -1;
+        const int64_t want = std::min<int64_t>(3 * n_cu, KS_PARTS) / n, from = ks_split_from(n, want);
+        if (from > 0 && Ta >= from && dev < KS_MAX_DEVICES && sdev == dev) {
+            len = (int)std::max<int64_t>(4 * KS_STEP, ((Ta + want - 1) / want + KS_STEP - 1) / KS_STEP * KS_STEP);
+            parts = (int)((Ta + (int64_t)len - 1) / len);
+        }
         // a captured launch may be replayed beside others: it keeps one work-group per row, and no slot
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (parts > 1 && (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) {
@@ -655,7 +690,8 @@ hipError_t launch_key_sens(int64_t n, int Ta, const float *grad, float *sens, hi
         }
     }
     auto launch = [&](int np, int nl, int slot) {
-        hipLaunchKernelGGL(key_sens_kernel, dim3((unsigned)(n * np)), dim3(KS_THREADS), 0, st, Ta, np, nl, slot, grad, sens);
+        hipLaunchKernelGGL(np > 1 ? key_sens_kernel<true> : key_sens_kernel<false>, dim3((unsigned)(n * np)), dim3(KS_THREADS),
+                           0, st, Ta, np, nl, slot, grad, sens);
         return hipGetLastError();
     };
     if (parts > 1 && ks_pool[dev].run(st, e, [&](int slot) { return launch(parts, len, slot); })) return e;

@@ -26,8 +26,12 @@ def _case(seed, n_tok, L, Hkv, Ta):
     return grad, grad.double().norm(dim=-1).mean(dim=-1)
 
 
-@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (1, 1, 3, 1023), (1, 1, 3, 1024), (2, 3, 2, 1025), (1, 1, 1, 9001),
-                                   (1, 19, 10, 1537), (1, 191, 1, 2049), (1, 24, 8, 1100)],
+# unsplit: the ends of rounds of 128 positions and of pairs of them; split: from 1536 positions (few rows), 1250
+# (36 rows), 1024 (72), 1152 (144) and 2560 (160 and 191) on
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (1, 300, 1, 128), (1, 300, 1, 129), (1, 30, 10, 256), (1, 1, 5, 257),
+                                   (1, 1, 2, 513), (1, 1, 3, 1535), (1, 1, 3, 1536), (2, 3, 2, 1537), (1, 36, 1, 1249),
+                                   (1, 36, 1, 1250), (1, 72, 1, 1023), (1, 72, 1, 1024), (1, 24, 8, 1100), (2, 36, 2, 1151),
+                                   (2, 36, 2, 1152), (1, 160, 1, 2559), (1, 160, 1, 2560), (1, 191, 1, 3001), (1, 1, 1, 9001)],
                          ids=lambda s: f"tok{s[0]}_L{s[1]}_kv{s[2]}_Ta{s[3]}")
 def test_split_rows(shape):
     import torch
