@@ -17,6 +17,7 @@
 #include "wnw.h"
 #include "wnw_internal.h"
 #include "wnw_lds.h"
+#include "wnw_screen.h"
 #include "wnw_slots.h"
 
 #include <float.h>
@@ -56,9 +57,7 @@ __device__ inline int vh_xcd_order(int w, int n)
 // which takes the rows that the screen cannot decide (hits = VH_OPEN on return).
 //
 // Bound.  A logit a from v_mfma_f32_32x32x16_bf16 differs from the exact e by at most
-// m = 2^-14 * |q|_1 * max |k|: the products are exact in fp32, and 127 additions that may each lose
-// a unit of the last place (2^-23) of at most sum |q_d k_d| lose under 2^-16 of it; the factor
-// four is margin for the order and alignment inside the instruction.  Keys are split into
+// m = 2^-14 * |q|_1 * max |k| (see wnw_screen.h).  Keys are split into
 // groups (per lane and register pair) of which the largest a is kept; if T is the K-th
 // largest of these maxima, K different keys have a >= T, hence e >= T - m, so a key of the
 // exact top K, ties included, has a >= T - 2 m.  m uses the largest key element seen up to the
@@ -80,7 +79,6 @@ __device__ inline int vh_xcd_order(int w, int n)
 constexpr int VH_OPEN = -1;
 constexpr int VF_THREADS = 512;
 constexpr int VF_CAP = 60;       // listed keys per row (60 keep two work-groups of RB = 4 in 160 KB)
-constexpr float VF_GAMMA = 0x1p-14f;
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 
 // Sum over the 16 lanes of a row of lanes (every lane ends with the same sum).
@@ -278,9 +276,7 @@ __global__ __launch_bounds__(VF_THREADS, RB == 4 ? 4 : 2) void voice_screen_kern
     }
     // rows outside the bound's range stay open, as those with too many keys
     {
-        const float kmax = __uint_as_float(sm.kmax << 16);
-        const bool in_range = sm.kmax < 0x7f80u && kmax >= 0x1p-60f && kmax < 0x1p60f && q1 >= 0x1p-60f && q1 < 0x1p60f;
-        if (ks == 0 && half == 0 && !in_range) sm.cnt[lrow] = VF_CAP + 1;
+        if (ks == 0 && half == 0 && !screen_in_range(q1, __uint_as_float(sm.kmax << 16))) sm.cnt[lrow] = VF_CAP + 1;
     }
     __syncthreads();
     // Exact logits of the listed keys: sixteen lanes a row, four keys in flight; lane i keeps the

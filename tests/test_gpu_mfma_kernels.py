@@ -30,6 +30,8 @@ HITS = [  # (L, H_q, H_kv, T_a, n_tok, K, what)
     (1, 8, 2, 5000, 9, 8, "same"),          # 200 equal best keys: the list overflows after a sample too
     (1, 8, 2, 1300, 9, 4, "big"),           # products beyond fp32
     (1, 8, 2, 1300, 9, 4, "tiny"),          # products below fp32's normal range
+    (1, 8, 2, 1300, 9, 4, "low"),           # products near fp32's normal range, just below the screen's range
+    (1, 8, 2, 1300, 9, 4, "lowest"),        # the smallest values that it takes
     (1, 8, 2, 1300, 9, 4, "cancel"),        # logits far below their products
     (1, 8, 2, 1300, 9, 4, "inf"),           # one infinite key element
 ]
@@ -59,6 +61,9 @@ def test_voice_screen_matches_oracle(shape):
     elif what == "tiny":
         kf *= np.float32(1e-20)
         qf *= np.float32(1e-19)
+    elif what in ("low", "lowest"):
+        kf *= np.float32(2.0 ** (-57 if what == "low" else -53))
+        qf *= np.float32(2.0 ** (-57 if what == "low" else -53))
     elif what == "cancel":
         # q . k = 0 for the bf16 values, up to a small last term
         h = gen.bf16_to_f32(gen.f32_to_bf16(qf))
