@@ -57,14 +57,17 @@ __device__ inline int vh_xcd_order(int w, int n)
 // which takes the rows that the screen cannot decide (hits = VH_OPEN on return).
 //
 // Bound.  A logit a from v_mfma_f32_32x32x16_bf16 differs from the exact e by at most
-// m = 2^-14 * |q|_1 * max |k| (see wnw_screen.h).  Keys are split into
+// m = 2^-14 * sum_d |q_d| kmax_d, kmax_d being the largest |k_d| of the keys (see wnw_screen.h).  Keys are split into
 // groups (per lane and register pair) of which the largest a is kept; if T is the K-th
 // largest of these maxima, K different keys have a >= T, hence e >= T - m, so a key of the
-// exact top K, ties included, has a >= T - 2 m.  m uses the largest key element seen up to the
-// key's own tile (and that of the sample, for T's side).
-//   sweep A  every third key (every second for K > 4): T from a sample spread over the audio;
-//   sweep B  every key: those with a >= T - 2 m go to the row's list;
-//   if a list overflowed: both again with T from every key;
+// exact top K, ties included, has a >= T - 2 m.
+//   sweep A  every third key (every second for K > 4): T and kmax_d from a sample spread over the audio;
+//   sweep B  every key: those with a >= T - 3 m go to the row's list, which leaves a key's own m twice the
+//            sample's; kmax_d of every key is taken along;
+//   if a list overflowed, or some kmax_d is over twice the sample's: both again, all from every key, with T - 2 m;
+// (one maximum over all channels instead of kmax_d makes m many times too large for keys with a few large
+// channels: with a constant 400 in one channel of normal keys most rows overflowed, 5.9 ms instead of the double
+// kernel's 4.4);
 // then the listed keys' logits in double (exact products, 16 lanes a key) and their ranks by
 // (value descending, position ascending).  A row stays open when its list overflows even then
 // (many keys within 2 m of each other, such as a zero query) or its values are not finite, too
@@ -74,7 +77,8 @@ __device__ inline int vh_xcd_order(int w, int n)
 // read from shared memory and 60 to 110 vector instructions (the scan of sixteen logits, the lists),
 // and a barrier per tile; the keys stream 1.3 to 2 times from HBM (1.2 GB on 240 KV-heads at 15000
 // positions: 0.25 ms at the rate of a large copy).  240 KV-heads, 15000 positions, 256 rows each, K = 4:
-// 4.37 ms with every logit in double, 0.55-0.6 ms here.  Eight wavefronts: RB blocks of 32 rows
+// 4.37-4.5 ms with every logit in double, 0.45-0.46 ms here (0.54 while every tile waited for a shared maximum over
+// all channels); also with constants of up to 1000 in a channel.  Eight wavefronts: RB blocks of 32 rows
 // times KS = 8 / RB shares of a tile's keys, so that a few rows still use the whole work-group.
 constexpr int VH_OPEN = -1;
 constexpr int VF_THREADS = 512;
@@ -104,8 +108,7 @@ struct VfSmem {
     int list[ROWS][VF_CAP];
     int cnt[ROWS];                                    // keys listed (those past VF_CAP are dropped)
     float thr[ROWS];                                  // T
-    unsigned kmax;                                    // largest key element so far, bf16 magnitude bits
-    int over;
+    alignas(16) unsigned kmax[D];                     // largest element per channel, bf16 magnitude bits
 };
 
 template <int RB>
@@ -147,25 +150,24 @@ __global__ __launch_bounds__(VF_THREADS, RB == 4 ? 4 : 2) void voice_screen_kern
         q1 += __shfl_xor(q1, 32);
     }
     if (tid < ROWS) sm.cnt[tid] = 0, sm.thr[tid] = -INFINITY;
-    if (tid == 0) sm.kmax = 0, sm.over = 0;
+    if (tid < D) sm.kmax[tid] = 0;
 
     float gm[8];                                      // maxima of this lane's groups
 #pragma unroll
     for (int i = 0; i < 8; ++i) gm[i] = -INFINITY;
-    float thr = -INFINITY, kms = 0.f;                 // T and the sample's largest key element
+    u16x2_t km[4] = {};                               // maxima of channels 8 (lane % 16) .. + 8 over the keys this lane reads
+    float lim = NAN;                                  // keys with a logit of at least this are listed (NaN: none)
+    bool in_range = false;                            // the bound holds for this row
 
     const unsigned tile0 = lds_address(&sm.tile[0][0]);
     const FragOffsets fo(lane);
     // One sweep over the keys 0, step, 2 step ...; LIST (step 1): append the keys at or above the threshold.
-    // The keys of a tile are looked at one iteration after their product, when the tile's largest
-    // element is known to all wavefronts (each takes a share of the dimensions).
+    // The keys of a tile are looked at one iteration after their product, whose result is there by then.
     auto sweep = [&](auto list_c, int step) {
         constexpr bool LIST = decltype(list_c)::value;
         auto look = [&](const f32x16_t &x, int k0) {
             // x[i]: key k0 + step * (32 ks + 8 (i / 4) + 4 half + i % 4) against row lrow
             if constexpr (LIST) {
-                // at least the lowest finite value: a masked key (-inf) is never listed
-                const float lim = fmaxf(thr - q1 * VF_GAMMA * (kms + __uint_as_float(*(volatile unsigned *)&sm.kmax << 16)), -FLT_MAX);
                 float mx = x[0];
 #pragma unroll
                 for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[i]);
@@ -203,22 +205,19 @@ __global__ __launch_bounds__(VF_THREADS, RB == 4 ? 4 : 2) void voice_screen_kern
             issue(t + NBUF - 1, buf == 0 ? NBUF - 1 : buf - 1);
             const int k0 = t * dk;
             if (t > 0) look(x, k0 - dk);
-            // this wavefront's share of the tile's elements, for their maximum (two bf16 magnitudes a word)
-            u16x2_t mx = {0, 0};
+            // this wavefront's share of the tile's rows for the channels' maxima (two bf16 magnitudes a word)
 #pragma unroll
             for (int j = 0; j < PF; ++j) {
-                const uint4 a = sm.tile[buf][(wave * PF + j) * 64 + lane];
+                const int r = (wave * PF + j) * 4 + (lane >> 4);
+                const uint4 a = sm.tile[buf][r * 16 + ((lane ^ r) & 15)];
                 const uint32_t d[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2_t, d[e] & 0x7fff7fffu));
+                for (int e = 0; e < 4; ++e) km[e] = __builtin_elementwise_max(km[e], __builtin_bit_cast(u16x2_t, d[e] & 0x7fff7fffu));
             }
             const unsigned fb = frag0 + (unsigned)buf * (TILE * D * 2);
             x = f32x16_t{};
 #pragma unroll
             for (int s = 0; s < 8; ++s) x = mfma32(frag_read(fb + fo.o[s]), __builtin_bit_cast(bf16x8_t, qf[s]), x);
-            const unsigned m = max((unsigned)mx.x, (unsigned)mx.y);
-            // a new maximum is rare after the first tiles: one ballot otherwise
-            if (__any(m > *(volatile unsigned *)&sm.kmax)) atomicMax(&sm.kmax, m);
             if (k0 + dk > Ta) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
@@ -230,9 +229,22 @@ __global__ __launch_bounds__(VF_THREADS, RB == 4 ? 4 : 2) void voice_screen_kern
         __syncthreads();
         look(x, (n - 1) * dk);
     };
-    // T: the K-th largest of the row's group maxima (-inf while fewer than K groups hold a key)
-    auto threshold = [&] {
+    // T: the K-th largest of the row's group maxima (-inf while fewer than K groups hold a key); then the limit
+    // T - margin * m
+    auto threshold = [&](float margin) {
         __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // the four lanes of a wavefront with these channels, then the wavefronts
+            unsigned m = __builtin_bit_cast(unsigned, km[e]);
+#pragma unroll
+            for (int o = 16; o < 64; o <<= 1)
+                m = __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, m), __builtin_bit_cast(u16x2_t, __shfl_xor(m, o))));
+            if (lane < 16) {
+                atomicMax(&sm.kmax[8 * lane + 2 * e], m & 0xffffu);
+                atomicMax(&sm.kmax[8 * lane + 2 * e + 1], m >> 16);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < 8; ++i) sm.gmax[lrow][ks * SM::GRP + half * 8 + i] = gm[i];
         __syncthreads();
@@ -250,34 +262,57 @@ __global__ __launch_bounds__(VF_THREADS, RB == 4 ? 4 : 2) void voice_screen_kern
             }
         }
         __syncthreads();
-        thr = row < R ? sm.thr[lrow] : INFINITY;      // a padding row lists nothing
-        kms = __uint_as_float(sm.kmax << 16);
+        float S = 0.f, mx = 0.f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const uint32_t d[4] = {qf[s].x, qf[s].y, qf[s].z, qf[s].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float k0 = __uint_as_float(sm.kmax[16 * s + 8 * half + 2 * e] << 16);
+                const float k1 = __uint_as_float(sm.kmax[16 * s + 8 * half + 2 * e + 1] << 16);
+                S = fmaf(fabsf(__uint_as_float(d[e] << 16)), k0, S);
+                S = fmaf(fabsf(__uint_as_float(d[e] & 0xffff0000u)), k1, S);
+                mx = fmaxf(mx, fmaxf(k0, k1));
+            }
+        }
+        S += __shfl_xor(S, 32);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        in_range = row < R && screen_in_range(S, q1, mx);
+        // at least the lowest finite value: a masked key (-inf) is never listed
+        lim = in_range ? fmaxf(sm.thr[lrow] - margin * VF_GAMMA * S, -FLT_MAX) : NAN;
     };
     // The sample's T lets about smp * K keys of a row pass, far under VF_CAP for nearly every row; an
     // overflow costs the work-group two more sweeps.  A short audio is its own sample.
     const int smp = Ta < 16 * TILE ? 1 : K <= 4 ? 3 : 2;
-    sweep(std::false_type{}, smp);
-    threshold();
-    sweep(std::true_type{}, 1);
-    __syncthreads();
-    if (smp > 1) {
-        if (tid < ROWS && sm.cnt[tid] > VF_CAP) sm.over = 1;
-        __syncthreads();
-        if (sm.over) {
-            // other groups than the sample's: a key is in one group only
-#pragma unroll
-            for (int i = 0; i < 8; ++i) gm[i] = -INFINITY;
-            sweep(std::false_type{}, 1);
-            threshold();
-            if (tid < ROWS) sm.cnt[tid] = 0;          // before the sweep's first barrier
+    if (__syncthreads_or(q1 > 0.f && q1 < INFINITY)) {
+        sweep(std::false_type{}, smp);
+        threshold(smp > 1 ? 3.f : 2.f);
+        if (__syncthreads_or(in_range)) {
             sweep(std::true_type{}, 1);
             __syncthreads();
+            if (smp > 1) {
+                bool again = tid < ROWS && sm.cnt[tid] > VF_CAP;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    // twice the sample's maximum, at most the largest finite value
+                    const unsigned ch = 8 * (lane & 15) + 2 * e;
+                    again |= km[e].x > min(sm.kmax[ch] + 0x80u, 0x7f7fu) || km[e].y > min(sm.kmax[ch + 1] + 0x80u, 0x7f7fu);
+                }
+                if (__syncthreads_or(again)) {
+                    // other groups than the sample's: a key is in one group only
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) gm[i] = -INFINITY;
+                    sweep(std::false_type{}, 1);
+                    threshold(2.f);
+                    if (tid < ROWS) sm.cnt[tid] = 0;   // before the sweep's first barrier
+                    sweep(std::true_type{}, 1);
+                    __syncthreads();
+                }
+            }
         }
     }
     // rows outside the bound's range stay open, as those with too many keys
-    {
-        if (ks == 0 && half == 0 && !screen_in_range(q1, __uint_as_float(sm.kmax << 16))) sm.cnt[lrow] = VF_CAP + 1;
-    }
+    if (ks == 0 && half == 0 && !in_range) sm.cnt[lrow] = VF_CAP + 1;
     __syncthreads();
     // Exact logits of the listed keys: sixteen lanes a row, four keys in flight; lane i keeps the
     // keys i, i + 16, ... and ranks them among all.

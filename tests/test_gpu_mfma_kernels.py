@@ -34,6 +34,16 @@ HITS = [  # (L, H_q, H_kv, T_a, n_tok, K, what)
     (1, 8, 2, 1300, 9, 4, "lowest"),        # the smallest values that it takes
     (1, 8, 2, 1300, 9, 4, "cancel"),        # logits far below their products
     (1, 8, 2, 1300, 9, 4, "inf"),           # one infinite key element
+    (32, 16, 8, 1031, 33, 4, "offset"),     # a large constant in two channels
+    (2, 8, 8, 4111, 3, 8, "offset"),
+    (32, 16, 8, 1031, 33, 4, "late"),       # large and first non-zero elements outside the sample: both sweeps again
+    (2, 8, 8, 4111, 3, 8, "late"),
+    (2, 8, 8, 4111, 3, 4, "late"),
+    (32, 16, 8, 1031, 33, 4, "edge"),       # channels and keys of zeros and subnormal values, one huge query element
+    (2, 8, 8, 4111, 3, 8, "edge"),
+    (2, 8, 2, 1300, 9, 4, "nan"),           # a NaN key element, a NaN and an infinite query: the other rows
+    (2, 8, 2, 4111, 9, 8, "nan"),
+    (2, 8, 2, 1300, 9, 4, "zeros"),         # a head whose keys are all zero
 ]
 
 
@@ -70,15 +80,41 @@ def test_voice_screen_matches_oracle(shape):
         qf = np.concatenate([h[..., :64], -h[..., :64]], axis=-1)
         kf[..., 64:] = kf[..., :64]
         kf[..., 127] += np.float32(0.01) * rng.standard_normal(kf.shape[:-1], dtype=np.float32)
+    elif what == "offset":
+        kf[..., 5] += 400
+        kf[..., 77] -= 400
+    elif what == "late":
+        # positions 101 and 407 are in no sample of every second or third key
+        kf[..., 9] = 0
+        kf[:, :, 101, 9] = 3
+        kf[:, :, 407, 20:40] *= 30
+    elif what == "edge":
+        kf[..., 3] = 0
+        kf[..., 4] *= np.float32(2.0 ** -128)
+        kf[:, :, 5:50] = 0
+        kf[:, :, 50:60] *= np.float32(2.0 ** -127)
+        qf[0, :, :, 3:5] = np.float32(2.0 ** 90)
+        qf[1] *= np.float32(2.0 ** -127)
+    elif what == "zeros":
+        kf[0, 0] = 0
     k, q = gen.f32_to_bf16(kf), gen.f32_to_bf16(qf)
+    ok = np.ones((n_tok, L, Hq), bool)
     if what == "inf":
         k[0, 0, 77, 5] = 0x7F80
+    elif what == "nan":
+        k[0, 0, 77, 5] = 0x7FC0
+        q[1, 1, 0, 7] = 0x7FC0
+        q[2, 1, 1, 7] = 0xFF80
+        ok[:, 0, : Hq // Hkv] = False
+        ok[1, 1, 0] = False                          # an infinite query: logits of +-inf tie by position
     a = rng.integers(0, Ta, size=n_tok)
     span = np.stack([a, np.minimum(a + rng.integers(1, 1 + Ta // 3, size=n_tok), Ta)], axis=1).astype(np.int32)
     hits = torch.full((n_tok, L, Hq), -7, dtype=torch.int32, device="cuda")
     W.wnw_voice_hits(to_dev(k), to_dev(q), torch.from_numpy(span).cuda(), K, Ta, hits)
     torch.cuda.synchronize()
-    bad = np.argwhere(hits.cpu().numpy() != O.voice_hits(k, q, span, K, Ta))
+    got = hits.cpu().numpy()
+    assert ((got >= 0) & (got <= K)).all()
+    bad = np.argwhere(ok & (got != O.voice_hits(k, q, span, K, Ta)))
     assert not len(bad), f"{len(bad)} of {hits.numel()} differ, first at (token, layer, q-head) {bad[0].tolist()}"
 
 
