@@ -381,8 +381,8 @@ __global__ __launch_bounds__(VF_THREADS, RB == 4 ? 4 : 2) void voice_screen_kern
     }
 }
 
-// Voice hits in double throughout, for the rows that the screen left open (a work-group whose rows
-// are all decided returns at once).
+// Voice hits in double throughout: for the rows that the screen left open (open_only; a work-group whose rows are
+// all decided returns at once), or for all rows where there was no screen.
 // Work-groups: ceil(n_tok * g / VH_ROWS) row blocks per KV-head (row = answer token * g + q-head
 // of the group), in XCD order so that the row blocks of one KV-head read its keys through one L2.
 // Wavefront w owns 16 rows of the block.  The logits run on v_mfma_f64_16x16x4f64 (lane
@@ -395,14 +395,15 @@ __global__ __launch_bounds__(VF_THREADS, RB == 4 ? 4 : 2) void voice_screen_kern
 // lane group) are merged at the end.  Products of bf16 values are exact in double.
 __global__ __launch_bounds__(NT, 4) void voice_hits_kernel(int L, int Hq, int Hkv, int T, int Ta, int n_tok, int K,
                                                        const uint16_t *__restrict__ k, const uint16_t *__restrict__ q,
-                                                       const int32_t *__restrict__ span, int32_t *__restrict__ hits)
+                                                       const int32_t *__restrict__ span, int32_t *__restrict__ hits,
+                                                       bool open_only)
 {
     const int g = Hq / Hkv, R = n_tok * g, nrb = (R + VH_ROWS - 1) / VH_ROWS;
     const int v = vh_xcd_order(blockIdx.x, gridDim.x), lk = v / nrb, rblk = v - lk * nrb;
     const int l = lk / Hkv, kv = lk - l * Hkv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kq = lane >> 4, li = lane & 15;
     const int r0 = rblk * VH_ROWS + wave * 16;
-    {
+    if (open_only) {
         const int rg = rblk * VH_ROWS + tid;
         const int t = rg / g, j = rg - t * g;
         const bool open = tid < VH_ROWS && rg < R && hits[((size_t)t * L + l) * Hq + (size_t)kv * g + j] == VH_OPEN;
@@ -787,14 +788,20 @@ wnw_status wnw_voice_hits(int32_t layers, int32_t q_heads, int32_t kv_heads, int
     if (!k_dev || !q_dev || !span_dev || !hits_dev) return triage_fail(WNW_ERR_INVALID, "NULL pointer");
     const int64_t R = (int64_t)n_tok * g, heads = (int64_t)layers * kv_heads;
     const int64_t nwg = (R + VH_ROWS - 1) / VH_ROWS * heads;
-    if ((R + 31) / 32 * heads > INT32_MAX) return triage_fail(WNW_ERR_UNSUPPORTED, "too many answer tokens for one launch");
-    const hipError_t es = launch_voice_screen(R, heads, (hipStream_t)hip_stream, layers, q_heads, kv_heads, rows, audio_len,
-                                              n_tok, top_k, (const uint16_t *)k_dev, (const uint16_t *)q_dev, span_dev,
-                                              hits_dev);
-    if (es != hipSuccess) return triage_fail(WNW_ERR_HIP, hipGetErrorString(es));
+    if (nwg > INT32_MAX) return triage_fail(WNW_ERR_UNSUPPORTED, "too many answer tokens for one launch");
+    // Short audio goes to the double kernel alone: the screen's fixed part (33 to 37 us) costs more than it
+    // saves.  With few rows 27 us against 33 on 64 positions and 35 against 34 on 128; with 61440 rows (256 on 240
+    // KV-heads) 43 against 45 us on 48 positions and 48 against 44 on 64.
+    const bool screen = audio_len >= (R * heads < 16384 ? 128 : 64) && (R + 31) / 32 * heads <= INT32_MAX;
+    if (screen) {
+        const hipError_t es = launch_voice_screen(R, heads, (hipStream_t)hip_stream, layers, q_heads, kv_heads, rows, audio_len,
+                                                  n_tok, top_k, (const uint16_t *)k_dev, (const uint16_t *)q_dev, span_dev,
+                                                  hits_dev);
+        if (es != hipSuccess) return triage_fail(WNW_ERR_HIP, hipGetErrorString(es));
+    }
     hipLaunchKernelGGL(voice_hits_kernel, dim3((unsigned)nwg), dim3(NT), 0,
                        (hipStream_t)hip_stream, layers, q_heads, kv_heads, rows, audio_len, n_tok, top_k,
-                       (const uint16_t *)k_dev, (const uint16_t *)q_dev, span_dev, hits_dev);
+                       (const uint16_t *)k_dev, (const uint16_t *)q_dev, span_dev, hits_dev, screen);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? WNW_OK : triage_fail(WNW_ERR_HIP, hipGetErrorString(e));
 }

@@ -22,6 +22,11 @@ HITS = [  # (L, H_q, H_kv, T_a, n_tok, K, what)
     (32, 16, 8, 1031, 33, 4, ""),           # 128 rows a work-group, a sample of the keys, ragged ends
     (32, 16, 8, 1024, 40, 8, "dup"),        # the same with keys that tie
     (32, 16, 8, 70, 33, 8, ""),             # the sample is all keys
+    (32, 16, 8, 63, 33, 8, ""),             # the double kernel alone, and just not (many rows)
+    (32, 16, 8, 64, 33, 8, "dup"),
+    (2, 8, 8, 127, 3, 4, "dup"),            # the same with few rows
+    (2, 8, 8, 128, 3, 4, ""),
+    (1, 8, 2, 5, 1, 4, ""),
     (32, 16, 8, 2051, 17, 4, ""),           # 64 rows a work-group
     (2, 8, 8, 4096, 3, 4, ""),              # 32 rows, eight shares of the keys, a sample
     (1, 24, 8, 4111, 1, 8, "dup"),
