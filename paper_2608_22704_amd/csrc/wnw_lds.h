@@ -48,8 +48,9 @@ __device__ inline void lds_tile_barrier()
 
 // Loader of tiles of TILE_ROWS rows: PF 16-byte pieces per lane, wavefront `wave` (uniform) taking pieces
 // 64 PF wave .. + 64 PF.  The lanes' offsets inside a tile are fixed, so a whole tile costs no vector
-// arithmetic: its base is uniform.
-template <int TILE_ROWS, int PF>
+// arithmetic: its base is uniform.  DIRECT needs rows aligned to 16 bytes, the size of its loads; otherwise the
+// pieces go through registers, for rows at any address that bf16 values may have.
+template <int TILE_ROWS, int PF, bool DIRECT = true>
 struct TileLoader {
     unsigned off[PF];
     int wave, lane, step;
@@ -63,6 +64,16 @@ struct TileLoader {
     {
         return (unsigned)src_row * (D * 2) + (unsigned)((lane ^ row(j)) & 15) * 16;
     }
+    __device__ void copy(const uint16_t *base, unsigned byte_off, unsigned lds) const
+    {
+        if constexpr (DIRECT)
+            load_to_lds(base, byte_off, lds);
+        else {
+            u32x4_t v;
+            __builtin_memcpy(&v, base + byte_off / 2, sizeof(v));
+            *(__attribute__((address_space(3))) u32x4_t *)(size_t)(lds + lane * 16) = v;
+        }
+    }
     // Rows row0, row0 + step, ... of `src` (rows of D, the last one rows - 1; row0 uniform, row0 + TILE_ROWS * step
     // < 2^31) into the tile at shared address `lds`.  Past the last row that row comes again.
     __device__ void load(const uint16_t *src, int row0, int rows, unsigned lds) const
@@ -71,13 +82,13 @@ struct TileLoader {
         if (row0 + step * TILE_ROWS <= rows) {
             const uint16_t *base = src + (size_t)row0 * D;
 #pragma unroll
-            for (int j = 0; j < PF; ++j) load_to_lds(base, off[j], lds + j * 1024);
+            for (int j = 0; j < PF; ++j) copy(base, off[j], lds + j * 1024);
         } else {
             const int first = min(row0, rows - 1);
             const uint16_t *base = src + (size_t)first * D;
 #pragma unroll
             for (int j = 0; j < PF; ++j)
-                load_to_lds(base, piece(j, min(row(j) * step, rows - 1 - first)), lds + j * 1024);
+                copy(base, piece(j, min(row(j) * step, rows - 1 - first)), lds + j * 1024);
         }
     }
 };

@@ -89,7 +89,7 @@ __device__ inline void merge_ms(float &m, float &l, float m2, float l2)
 // row's running (max, sum) is a single pair per lane and block; the two lanes of a row merge at the
 // end.  NB = 2 halves the shared-memory reads per product; NB = 1 is for launches of few work-groups
 // (72 KV-heads, 1176 rows, 3754 keys: 112 us with 1, 121 with 2, 146 with 16 x 16 products).
-template <int NB>
+template <int NB, bool DIRECT>
 __global__ __launch_bounds__(NT, NB == 2 ? 2 : 3) void prefill_rowstats_kernel(Geometry g, const uint16_t *__restrict__ K,
                                                                               const uint16_t *__restrict__ qt,
                                                                               float *__restrict__ stat)
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(NT, NB == 2 ? 2 : 3) void prefill_rowstats_kernel(G
 
     __shared__ alignas(256) uint4 kbuf[PBUF][PT * (D / 8)];
     const unsigned tile0 = lds_address(&kbuf[0][0]);
-    const TileLoader<PT, PPF> ld(wave, lane, 1);
+    const TileLoader<PT, PPF, DIRECT> ld(wave, lane, 1);
     auto issue = [&](int t, int buf) { ld.load(Kh, t * PT, g.T, tile0 + (unsigned)buf * (PT * D * 2)); };
     bf16x8_t qf[NB][8];
     int lim[NB];                                      // causal limit (last visible key) of the row
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(NT, NB == 2 ? 2 : 3) void prefill_rowstats_kernel(G
 // KB = 4 feeds more products per fragment read; KB = 3 cuts a small cache into more work-groups
 // (measured, both passes together: 240 KV-heads, 15000 keys, 2048 rows 3.59 ms with 4, 3.66 with 3; 72
 // KV-heads, 3607 keys, 1176 rows 192 us with 4, 187 with 3).
-template <int KB>
+template <int KB, bool DIRECT>
 __global__ __launch_bounds__(NT, 3) void prefill_colsum_kernel(Geometry g, const uint16_t *__restrict__ K,
                                                                const uint16_t *__restrict__ qt,
                                                                const float *__restrict__ stat, float *__restrict__ p)
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(NT, 3) void prefill_colsum_kernel(Geometry g, const
     __shared__ alignas(16) float sbuf[PBUF][4][PT];
     static_assert(PT == 64, "one row statistic per lane and tile");
     const unsigned tile0 = lds_address(&qbuf[0][0]), stat0 = lds_address(&sbuf[0][wave][0]);
-    const TileLoader<PT, PPF> ld(wave, lane, 1);
+    const TileLoader<PT, PPF, DIRECT> ld(wave, lane, 1);
     auto issue = [&](int t, int buf) {
         ld.load(Qh, t * PT, R, tile0 + (unsigned)buf * (PT * D * 2));
         load_word_to_lds(stat + qbase, (unsigned)min(t * PT + lane, R - 1) * 4, stat0 + (unsigned)buf * (unsigned)sizeof(sbuf[0]));
@@ -446,16 +446,22 @@ hipError_t launch_prefill_scores(const Geometry &g, const uint16_t *K, const uin
     // pass 2: KB = 4 from eight work-groups a compute unit up
     const long long n2 = (long long)((g.Ta + 255) / 256) * nheads, n2s = (long long)((g.Ta + 191) / 192) * nheads;
     if (n1s > INT32_MAX || n2s > INT32_MAX) return hipErrorInvalidValue;
-    if (n1 >= 4LL * std::max(g.n_cu, 1))
-        hipLaunchKernelGGL(prefill_rowstats_kernel<2>, dim3((unsigned)n1), dim3(NT), 0, st, g, K, q_text, lse);
+    // rows that are not aligned to the loads straight into shared memory: through registers (one variant each)
+    const bool direct = (((uintptr_t)K | (uintptr_t)q_text) & 15) == 0;
+    if (!direct)
+        hipLaunchKernelGGL((prefill_rowstats_kernel<1, false>), dim3((unsigned)n1s), dim3(NT), 0, st, g, K, q_text, lse);
+    else if (n1 >= 4LL * std::max(g.n_cu, 1))
+        hipLaunchKernelGGL((prefill_rowstats_kernel<2, true>), dim3((unsigned)n1), dim3(NT), 0, st, g, K, q_text, lse);
     else
-        hipLaunchKernelGGL(prefill_rowstats_kernel<1>, dim3((unsigned)n1s), dim3(NT), 0, st, g, K, q_text, lse);
+        hipLaunchKernelGGL((prefill_rowstats_kernel<1, true>), dim3((unsigned)n1s), dim3(NT), 0, st, g, K, q_text, lse);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (n2 >= 8LL * std::max(g.n_cu, 1))
-        hipLaunchKernelGGL(prefill_colsum_kernel<4>, dim3((unsigned)n2), dim3(NT), 0, st, g, K, q_text, (const float *)lse, p);
+    if (!direct)
+        hipLaunchKernelGGL((prefill_colsum_kernel<3, false>), dim3((unsigned)n2s), dim3(NT), 0, st, g, K, q_text, (const float *)lse, p);
+    else if (n2 >= 8LL * std::max(g.n_cu, 1))
+        hipLaunchKernelGGL((prefill_colsum_kernel<4, true>), dim3((unsigned)n2), dim3(NT), 0, st, g, K, q_text, (const float *)lse, p);
     else
-        hipLaunchKernelGGL(prefill_colsum_kernel<3>, dim3((unsigned)n2s), dim3(NT), 0, st, g, K, q_text, (const float *)lse, p);
+        hipLaunchKernelGGL((prefill_colsum_kernel<3, true>), dim3((unsigned)n2s), dim3(NT), 0, st, g, K, q_text, (const float *)lse, p);
     return hipGetLastError();
 }
 

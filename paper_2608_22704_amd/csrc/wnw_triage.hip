@@ -792,7 +792,9 @@ wnw_status wnw_voice_hits(int32_t layers, int32_t q_heads, int32_t kv_heads, int
     // Short audio goes to the double kernel alone: the screen's fixed part (33 to 37 us) costs more than it
     // saves.  With few rows 27 us against 33 on 64 positions and 35 against 34 on 128; with 61440 rows (256 on 240
     // KV-heads) 43 against 45 us on 48 positions and 48 against 44 on 64.
-    const bool screen = audio_len >= (R * heads < 16384 ? 128 : 64) && (R + 31) / 32 * heads <= INT32_MAX;
+    // Keys that are not aligned to the screen's loads (16 bytes, straight into shared memory) go there as well.
+    const bool screen = audio_len >= (R * heads < 16384 ? 128 : 64) && (R + 31) / 32 * heads <= INT32_MAX &&
+                        ((uintptr_t)k_dev & 15) == 0;
     if (screen) {
         const hipError_t es = launch_voice_screen(R, heads, (hipStream_t)hip_stream, layers, q_heads, kv_heads, rows, audio_len,
                                                   n_tok, top_k, (const uint16_t *)k_dev, (const uint16_t *)q_dev, span_dev,

@@ -168,3 +168,42 @@ def test_prefill_scores_match_oracle(shape):
         rel = np.abs(got[l, h] - ref) / np.maximum(ref, 2.0 ** -100)   # terms below 2^-190 flush
         log(f"[prefill] head ({l},{h}): max rel err {rel.max():.3g} of {tol:.3g}")
         assert (rel <= tol).all()
+
+
+def _at_offset(t, n):
+    """The same values n elements past an aligned address."""
+    import torch
+    u = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
+    assert u.data_ptr() % 16 == 0
+    return u[n: n + t.numel()].view(t.shape).copy_(t)
+
+
+@pytest.mark.parametrize("off", [(1, 0), (0, 1), (2, 3), (4, 8)], ids=lambda o: f"k{o[0]}_q{o[1]}")
+def test_rows_at_any_address(off):
+    """Keys and queries that start between multiples of 16 bytes, the size of the loads straight into
+    shared memory: the same results as aligned ones."""
+    import torch
+    from paper_2608_22704_amd import wnw as W
+    from tests.wnw_harness import log
+    log(f"[case] prefill scores and voice hits, rows {off} elements past 16 bytes")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    L, Hq, Hkv, Ta, Tt, n_tok, K = 2, 8, 2, 515, 70, 9, 4
+    k = torch.randn((1, L, Hkv, Ta + Tt, 128), generator=g, device="cuda").bfloat16()
+    q = torch.randn((1, L, Hq, Tt, 128), generator=g, device="cuda").bfloat16()
+    qa = torch.randn((n_tok, L, Hq, 128), generator=g, device="cuda").bfloat16()
+    span = torch.tensor([[50 * i, 50 * i + 40] for i in range(n_tok)], dtype=torch.int32, device="cuda")
+    got = []
+    for ko, qo in ((0, 0), off):
+        kd, qd, qad = _at_offset(k, ko), _at_offset(q, qo), _at_offset(qa, qo)
+        ctx = W.wnw_init_cache(W.make_config(1, L, Hq, Hkv, Ta, Tt, 32, 2000), kd, kd)
+        try:
+            sc = torch.full((1, L, Hkv, Ta), -1.0, device="cuda")
+            W.wnw_prefill_scores(ctx, qd, sc)
+            hits = torch.full((n_tok, L, Hq), -7, dtype=torch.int32, device="cuda")
+            W.wnw_voice_hits(kd[0], qad, span, K, Ta, hits)
+            torch.cuda.synchronize()
+            got.append((sc, hits))
+        finally:
+            W.wnw_destroy(ctx)
+    assert bool(torch.isfinite(got[0][0]).all()) and bool((got[0][1] >= 0).all())
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
