@@ -26,11 +26,11 @@ __device__ inline unsigned lds_address(const void *p)
 // read of shared memory; the kernels wait themselves (lds_loads_wait).  There is no register output.
 __device__ inline void load_to_lds(const void *base, unsigned off, unsigned lds)
 {
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0", "memory");
 }
 __device__ inline void load_word_to_lds(const void *base, unsigned off, unsigned lds)
 {
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0", "memory");
 }
 
 // Waits until at most N of this wavefront's vector memory loads are outstanding.
