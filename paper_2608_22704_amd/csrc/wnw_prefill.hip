@@ -165,13 +165,16 @@ __global__ __launch_bounds__(NT, NB == 2 ? 2 : 3) void prefill_rowstats_kernel(G
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
                 float mt = -INFINITY;
+                bool nan = false;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     if (k0 + 8 * (i / 4) + 4 * half + i % 4 > lim[n]) x[n][i] = -INFINITY;
                     mt = fmaxf(mt, x[n][i]);
+                    nan |= x[n][i] != x[n][i];
                 }
-                if (mt == -INFINITY) continue;           // every key masked for this row
-                const float mn = fmaxf(-nm[n], mt * C2);
+                if (mt == -INFINITY && !nan) continue;   // every key masked for this row
+                // a visible NaN (which the maximum passes over) makes the sum NaN, with a maximum that is kept
+                const float mn = nan ? 0.f : fmaxf(-nm[n], mt * C2);
                 float acc = sum[n] * exp2_hw(-nm[n] - mn);   // exp2(-inf) = 0 for an empty row
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc += exp2_hw(fmaf(x[n][i], C2, -mn));

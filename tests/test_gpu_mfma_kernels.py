@@ -207,3 +207,39 @@ def test_rows_at_any_address(off):
             W.wnw_destroy(ctx)
     assert bool(torch.isfinite(got[0][0]).all()) and bool((got[0][1] >= 0).all())
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("what", ["text key", "audio key", "query", "infinite text key"])
+@pytest.mark.parametrize("Ta,Tt", [(96, 1), (64, 1), (7, 1), (128, 40), (515, 70)])
+def test_prefill_nan_stays_nan(Ta, Tt, what):
+    """A NaN (or infinite) element that a row sees makes every score of its KV-head NaN; the other heads'
+    scores are those of clean inputs."""
+    import torch
+    from paper_2608_22704_amd import wnw as W
+    from tests.wnw_harness import log
+    log(f"[case] prefill scores with a bad {what}, Ta {Ta} Tt {Tt}")
+    g = torch.Generator(device="cuda").manual_seed(Ta)
+    L, Hq, Hkv = 2, 6, 2
+    k = torch.randn((1, L, Hkv, Ta + Tt, 128), generator=g, device="cuda").bfloat16()
+    q = torch.randn((1, L, Hq, Tt, 128), generator=g, device="cuda").bfloat16()
+    got = []
+    for bad in (False, True):
+        if bad and what == "query":
+            q[0, 1, 1, Tt - 1, 9] = float("nan")     # q-head 1 of KV-head 0
+        elif bad and what == "infinite text key":
+            k[0, 1, 0, Ta, 9] = float("inf")
+            q[0, 1, 0, 0, 9] = 1.0
+        elif bad:
+            k[0, 1, 0, Ta if what == "text key" else Ta - 1, 9] = float("nan")
+        ctx = W.wnw_init_cache(W.make_config(1, L, Hq, Hkv, Ta, Tt, 32, 2000), k, k)
+        try:
+            sc = torch.full((1, L, Hkv, Ta), -1.0, device="cuda")
+            W.wnw_prefill_scores(ctx, q, sc)
+            torch.cuda.synchronize()
+            got.append(sc[0])
+        finally:
+            W.wnw_destroy(ctx)
+    assert bool(torch.isfinite(got[0]).all())
+    assert bool(torch.isnan(got[1][1, 0]).all())
+    got[1][1, 0] = got[0][1, 0]
+    assert torch.equal(got[0], got[1])
