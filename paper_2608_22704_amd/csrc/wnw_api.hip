@@ -627,11 +627,18 @@ wnw_status wait_copies(wnw_ctx *c, int par, hipStream_t s)
 // Whether a step runs the mass merge and the selection inside the launch of its anchor tiles: while
 // those tiles all fit the chip at once (two work-groups a compute unit), so that the wait of each
 // for its stores and its arrival delays no tile behind it (on 2928 tiles that wait cost the launch
-// 7 us, as much as it saves).  With next-step timing and host-issued copies the selection has the
-// tidal/fixed launch to run in.
+// 7 us, as much as it saves), and with no more chunks and segments than the work-group has threads (one
+// layer, same-step: 256 chunks 36.1 us against 41.3 with the select kernel's 1024 threads, 258 chunks 44.5
+// against 37.4).  More of them only beside static tiles that take longer than the selection: next-step, 258
+// chunks, one layer (250 tiles times q-heads per KV-head) 55.3 against 47.0, 4 layers (1220) 57.7 against 55.6,
+// 6 layers of 4 x 8 heads (2460) 64.1 against 64.5, 36 layers of 2 x 8 (7280) 76.0 against 83.1; 340 chunks, 6
+// layers (3170) 66.5 against 70.4.  With next-step timing and host-issued copies the selection has the tidal/fixed
+// launch to run in.
 bool select_with_anchors(const Geometry &g, bool memcpy_path)
 {
-    return !(g.next_step && memcpy_path) && (int64_t)g.n_tiles_a * g.nA * g.B <= 2ll * g.n_cu && anchor_select_fits(g);
+    const bool hidden = g.next_step && (int64_t)g.n_static * g.B * g.G >= 10ll * g.n_cu;
+    return !(g.next_step && memcpy_path) && (int64_t)g.n_tiles_a * g.nA * g.B <= 2ll * g.n_cu &&
+           (hidden || std::max(g.nc, g.nchk) <= NT) && anchor_select_fits(g);
 }
 
 // The recall thread's loop (see wnw_ctx::RecallJob).

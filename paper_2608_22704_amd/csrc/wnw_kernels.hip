@@ -886,12 +886,13 @@ __device__ inline void select_seq(const Geometry &g, const StepBuffers &s, float
             if (c >= 0 && c < nk) fsel[c] = 1;
         }
     } else {
-        // Counting takes nk^2 comparisons over the work-group, the search 48 nk / 64 in one wavefront: on
-        // 235 chunks 4.2 against 3.0 us with 256 threads, 2.5 against 2.6 with 1024; on 32 chunks 0.7
-        // against 2.0; on 703 chunks the search takes 6.7 us.
-        if (nk > 128 && nk <= 256 && nthr <= 256)
+        // Counting takes nk^2 comparisons over the work-group, the search 48 nk / 64 in one wavefront.  Whole steps
+        // of one layer, counting and search: with 256 threads (tidal launch) 130 chunks 27.4 and 27.9 us, 160 28.0
+        // and 28.0, 200 29.5 and 28.7, 256 31.1 and 28.9, 300 38.3 and 38.4, 380 43.8 and 40.6; with 1024 threads 300
+        // chunks 38.1 and 41.5, 380 41.1 and 43.0, 450 44.5 and 44.2, 600 54.5 and 51.2, 760 61.1 and 52.7.
+        if (nk > 160 && nk <= 256 && nthr <= 256)
             top_k_wave<4>(ckey, nk, k, fsel);
-        else if (nk > 256 && nk <= 768)
+        else if (nk > (nthr <= 256 ? 256 : 420) && nk <= 768)
             top_k_wave<12>(ckey, nk, k, fsel);
         else {
             // rank of every chunk among all (the number of larger keys): P adjacent lanes per chunk

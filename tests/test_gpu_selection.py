@@ -16,7 +16,7 @@ def _gpu():
 
 @pytest.mark.parametrize("mode", ["same", "next", "next_copies"])
 @pytest.mark.parametrize("big", [False, True], ids=["small", "large"])
-@pytest.mark.parametrize("n", [3, 64, 128, 129, 256, 257, 768, 769, 1000])
+@pytest.mark.parametrize("n", [3, 64, 160, 161, 256, 257, 420, 421, 768, 769, 1000])
 def test_selection_follows_the_scores(n, big, mode):
     import torch
     from paper_2608_22704_amd import wnw as W
