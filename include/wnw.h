@@ -45,7 +45,9 @@
  * serialised by the caller.
  *
  * Environment: WNW_LOG=1 prints one trace line per decode step on stderr (what the call
- * enqueued; with WNW_F_RECALL_MEMCPY the segments it copied and the host's wait).
+ * enqueued; with WNW_F_RECALL_MEMCPY the segments it copied and the host's wait; where the
+ * selection ran: "inside the anchor launch", "inside the tidal launch", or in kernels of its own
+ * "before the tidal launch").
  * WNW_TEST_PINNED_LIMIT=<bytes> makes pinned allocations above that size fail with WNW_ERR_OOM
  * (a test hook for the failure path of wnw_set_roles).
  */
@@ -191,7 +193,9 @@ typedef struct {
     int64_t selections_in_tidal; /* steps whose anchor mass merge and selection ran inside the
                                   tidal/fixed launch (WNW_F_SELECT_NEXT_STEP with
                                   WNW_F_RECALL_MEMCPY, after a previous-step recall of at most
-                                  4 MiB); the other steps ran the two kernels before it         */
+                                  4 MiB); the other steps ran them before it, in two kernels or,
+                                  on small caches without that pair of flags, inside the first
+                                  launch                                                        */
 } wnw_stats;
 
 /* Create a context for one batch of caches: the full KV cache as prefill leaves it, before any
@@ -367,7 +371,9 @@ void wnw_destroy(wnw_ctx *ctx);
 
 /* Voice-score hits.  For every answer token t and q-head (l, h): the top_k audio positions with
  * the largest logit q . k (the softmax keeps that order; ties to the lower position), and how
- * many lie in [span[t][0], span[t][1]).  Logits are exact bf16 products summed in double.
+ * many lie in [span[t][0], span[t][1]).  Every decision among keys that can be among the top_k is
+ * made on exact bf16 products summed in double; keys that an error bound on products summed in fp32
+ * excludes are not evaluated further.
  *   k_dev     device bf16 [L][H_kv][rows][d] of one calibration sample, audio rows first
  *   q_dev     device bf16 [n_tok][L][H_q][d], the answer tokens' queries
  *   span_dev  device int32 [n_tok][2], audio-token interval [a, b) of each answer token

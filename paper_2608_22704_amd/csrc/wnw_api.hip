@@ -1502,7 +1502,8 @@ wnw_status wnw_decode_step(wnw_ctx *c, const void *q_dev, void *out, float *scor
                         "total, selection %s\n",
                 (long long)c->steps, g.next_step ? "next-step" : "same-step",
                 memcpy_path ? "copy-engine" : "work-group", g.B, n_new, c->host_wait_ms,
-                sel_in_tidal ? "inside the tidal launch" : "before the tidal launch");
+                g.nc == 0 ? "none" : sel_in_tidal ? "inside the tidal launch"
+                                 : sel_with_anchors ? "inside the anchor launch" : "before the tidal launch");
     }
     c->steps++;
     return WNW_OK;

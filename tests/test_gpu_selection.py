@@ -1,6 +1,10 @@
 """GPU test of the selection's ranking and slot assignment at the chunk counts where they change method, in
-every place the selection runs (its own kernel, the anchor tiles' launch, the tidal launch).  The chunk
-scores that the step reports fix the selection exactly; residency and slot bytes follow from it."""
+the three places the selection runs: inside the anchor tiles' launch (up to 256 chunks here; several anchor
+heads and sequences, so that its arrivals chain), inside the tidal launch, and in kernels of its own.  Each
+case checks from the library's trace that the selection ran where it should.  The chunk scores that the step
+reports fix the selection exactly; residency and slot bytes follow from it."""
+import re
+
 import numpy as np
 import pytest
 
@@ -16,50 +20,58 @@ def _gpu():
 
 @pytest.mark.parametrize("mode", ["same", "next", "next_copies"])
 @pytest.mark.parametrize("big", [False, True], ids=["small", "large"])
-@pytest.mark.parametrize("n", [3, 64, 160, 161, 256, 257, 420, 421, 768, 769, 1000])
-def test_selection_follows_the_scores(n, big, mode):
+@pytest.mark.parametrize("n", [3, 64, 128, 129, 160, 161, 256, 257, 420, 421, 768, 769, 1000])
+def test_selection_follows_the_scores(n, big, mode, capfd, monkeypatch):
     import torch
     from paper_2608_22704_amd import wnw as W
     from tests.wnw_harness import log
     log(f"[case] selection over {n} chunks, {mode}, {'many' if big else 'few'} anchor tiles")
     # `large`: more anchor tiles than the chip holds at once, so that the selection has its own kernel
-    L, Hq, Hkv, cl, Tt, delta = (80 if big else 1), 8, 4, 2, (5000 if big else 8), 3
+    B, L, Hq, Hkv, cl, Tt, delta = (1 if big else 2), (80 if big else 3), 8, 4, 2, (5000 if big else 8), 3
     Ta, k = n * cl, max(1, n // 5)
     flags = {"same": 0, "next": W.WNW_F_SELECT_NEXT_STEP,
              "next_copies": W.WNW_F_SELECT_NEXT_STEP | W.WNW_F_RECALL_MEMCPY}[mode]
+    # the arrays of 420 chunks and more do not fit the tidal launch's shared memory
+    where = ("inside the tidal launch" if mode == "next_copies" and n < 420 else
+             "inside the anchor launch" if mode != "next_copies" and n <= 256 and not big else "before the tidal launch")
     g = torch.Generator(device="cuda").manual_seed(n)
-    kv = [torch.randn((1, L, Hkv, Ta + Tt, 128), generator=g, device="cuda").bfloat16() for _ in range(2)]
+    kv = [torch.randn((B, L, Hkv, Ta + Tt, 128), generator=g, device="cuda").bfloat16() for _ in range(2)]
     roles = np.full((L, Hkv), W.WNW_FIXED, np.uint8)
     roles[:, 0] = W.WNW_ANCHOR
     roles[0, 1:3] = W.WNW_TIDAL
-    pf = torch.rand((1, L, Hkv, Ta), generator=g, device="cuda")
-    ctx = W.wnw_init_cache(W.make_config(1, L, Hq, Hkv, Ta, Tt, cl, 5000, top_k=k, flags=flags), *kv)
+    pf = torch.rand((B, L, Hkv, Ta), generator=g, device="cuda")
+    monkeypatch.setenv("WNW_LOG", "1")
+    ctx = W.wnw_init_cache(W.make_config(B, L, Hq, Hkv, Ta, Tt, cl, 5000, top_k=k, flags=flags), *kv)
     try:
         W.wnw_set_roles_device(ctx, roles, pf)
         cb = W.wnw_query_geometry(ctx)["chunk_bytes"]
-        out = torch.empty((1, L, Hq, 128), device="cuda")
-        sc = torch.empty((1, n), device="cuda")
-        sel = torch.full((1, k), -5, dtype=torch.int32, device="cuda")
-        picked = []
+        out = torch.empty((B, L, Hq, 128), device="cuda")
+        sc = torch.empty((B, n), device="cuda")
+        sel = torch.full((B, k), -5, dtype=torch.int32, device="cuda")
+        picked = [[] for _ in range(B)]
         for s in range(6):
             # step 1: zero queries, every chunk ties with its equals and the lowest ids win
-            q = torch.randn((1, L, Hq, 128), generator=g, device="cuda") * (0.0 if s == 1 else 1.0)
+            q = torch.randn((B, L, Hq, 128), generator=g, device="cuda") * (0.0 if s == 1 else 1.0)
             W.wnw_decode_step(ctx, q.bfloat16(), out, sc, sel)
             torch.cuda.synchronize()
-            v = sc.cpu().numpy()[0]
-            want = np.sort(np.lexsort((np.arange(n), -v))[:k])
-            assert np.array_equal(sel.cpu().numpy()[0], want), f"step {s}"
-            picked.append(set(want.tolist()))
-        resident = set().union(*picked[-delta:])
-        flags_dev = np.zeros((1, n), np.uint8)
+            for b in range(B):
+                v = sc.cpu().numpy()[b]
+                want = np.sort(np.lexsort((np.arange(n), -v))[:k])
+                assert np.array_equal(sel.cpu().numpy()[b], want), f"step {s}, sequence {b}"
+                picked[b].append(set(want.tolist()))
+        flags_dev = np.zeros((B, n), np.uint8)
         W.wnw_debug_read_resident(ctx, flags_dev)
-        seen = set().union(*picked[-delta - 1: -1]) if flags else resident
-        assert set(np.nonzero(flags_dev[0])[0].tolist()) == seen
-        a, b = np.empty(cb, np.uint8), np.empty(cb, np.uint8)
-        for c in sorted(resident)[:: max(1, len(resident) // 16)]:
-            W.wnw_debug_read_slot(ctx, 0, c, a, cb)
-            W.wnw_debug_read_host_chunk(ctx, 0, c, b, cb)
-            assert np.array_equal(a, b), f"segment {c}"
+        x, y = np.empty(cb, np.uint8), np.empty(cb, np.uint8)
+        for b in range(B):
+            resident = set().union(*picked[b][-delta:])
+            seen = set().union(*picked[b][-delta - 1: -1]) if flags else resident
+            assert set(np.nonzero(flags_dev[b])[0].tolist()) == seen, f"sequence {b}"
+            for c in sorted(resident)[:: max(1, len(resident) // 16)]:
+                W.wnw_debug_read_slot(ctx, b, c, x, cb)
+                W.wnw_debug_read_host_chunk(ctx, b, c, y, cb)
+                assert np.array_equal(x, y), f"sequence {b}, segment {c}"
         assert W.wnw_get_stats(ctx)["slot_exhausted"] == 0
     finally:
         W.wnw_destroy(ctx)
+    ran = re.findall(r"^\[wnw\] step .* selection (.+)$", capfd.readouterr().err, re.M)
+    assert ran == [where] * 6, ran
