@@ -17,12 +17,15 @@
 //
 // What bounds it: per logit and pass, an FMA, an exponential and an addition next to 256 flop on the
 // matrix cores, and the chip's power: on 240 KV-heads, 15000 keys and 2048 rows the clock falls to
-// 1.6-1.7 GHz, with the matrix cores busy 50-57 % of the cycles and the vector unit 65-75 %.  There both
-// passes took 4.06-4.4 ms staged through registers with 16 x 16 products in pass 1, and take 3.45-3.6 ms
-// now (3.8 TFLOP executed: 1.1 PFLOP/s, what a bf16 matrix product of 8192 reaches on the card); on 72
-// KV-heads, 3607 keys and 1176 rows 205-215 us, now 178-187 us.  A loop that takes one product's terms
-// between the next one's matrix instructions, at two work-groups a compute unit, was slower (3.9 ms):
-// three work-groups overlap the two units better.
+// 1.6-1.7 GHz, with the matrix cores busy 50-57 % of the cycles and vector instructions issued on 45 % of
+// them (counting four cycles each; an exponential holds the unit longer).  There both passes took 4.06-4.4 ms
+// staged through registers with 16 x 16 products in pass 1, and take 3.41-3.63 ms now, 3.9 on the
+// benchmark's inputs (3.8 TFLOP executed: 1.0-1.1 PFLOP/s; a bf16 matrix product of 8192 reaches 1.18 on the card);
+// on 72 KV-heads, 3607 keys and 1176 rows 205-215 us, now 178-187 us.  There the tiles in flight are not quite
+// kept there: the fragments loaded before the loop are first used in it, and the compiler waits for every load
+// in the first of three tiles of each round.  A loop that takes one product's terms between the next one's
+// matrix instructions, at two work-groups a compute unit, was slower (3.9 ms): three work-groups overlap the two
+// units better.
 #include "wnw_internal.h"
 #include "wnw_lds.h"
 
@@ -444,9 +447,15 @@ hipError_t launch_prefill_scores(const Geometry &g, const uint16_t *K, const uin
         return hipGetLastError();
     }
     const long long nheads = (long long)g.B * g.L * g.Hkv;
-    // pass 1: work-groups of 256 rows; of 128 where they would leave the device short
+    // Pass 1: work-groups of 256 rows from four of them a compute unit up, of 128 below.  Smaller ones cost from
+    // 4.5 a unit up (72 KV-heads, 4096 rows, 7500 keys: +36 us of 1075; 240 KV-heads, 1200 rows, 3607 keys: +43 of 553) and
+    // gain up to 1.4 (72 KV-heads, 1176 rows, 15000 keys: -11 of 677; 8 KV-heads, 1536 rows, 15000 keys: -109 of
+    // 369).  Between, the rows that fill the last work-group decide (at 2.8 a unit -43 of 1249 us with 588 rows a head,
+    // +24 of 655 with 2400; at 1.9 +7 to +13 of 71 to 150).
     const long long n1 = (long long)((R + 255) / 256) * nheads, n1s = (long long)((R + 127) / 128) * nheads;
-    // pass 2: KB = 4 from eight work-groups a compute unit up
+    // Pass 2: KB = 4 from eight work-groups of 256 keys a compute unit up, 3 below.  KB = 3 costs 5 to 20 us from 8.4 a
+    // unit up on 72 KV-heads (1075 us: +17; 2042: +43) and gains 5 to 17 at 4.2 (187 us: -5; 585: -17); with the last round
+    // of work-groups nearly empty it goes the other way (240 KV-heads, 3607 keys: -9 to -21 of 308 to 928 at 14).
     const long long n2 = (long long)((g.Ta + 255) / 256) * nheads, n2s = (long long)((g.Ta + 191) / 192) * nheads;
     if (n1s > INT32_MAX || n2s > INT32_MAX) return hipErrorInvalidValue;
     // rows that are not aligned to the loads straight into shared memory: through registers (one variant each)

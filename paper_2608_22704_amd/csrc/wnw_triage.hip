@@ -73,12 +73,13 @@ __device__ inline int vh_xcd_order(int w, int n)
 // (many keys within 2 m of each other, such as a zero query) or its values are not finite, too
 // large or too small for the bound.
 //
-// What bounds it: one 32 x 32 x 128 product per wavefront and tile is 8 matrix instructions against 10 KB
-// read from shared memory and 60 to 110 vector instructions (the scan of sixteen logits, the lists),
-// and a barrier per tile; the keys stream 1.3 to 2 times from HBM (1.2 GB on 240 KV-heads at 15000
-// positions: 0.25 ms at the rate of a large copy).  240 KV-heads, 15000 positions, 256 rows each, K = 4:
-// 4.37-4.5 ms with every logit in double, 0.45-0.46 ms here (0.54 while every tile waited for a shared maximum over
-// all channels); also with constants of up to 1000 in a channel.  Eight wavefronts: RB blocks of 32 rows
+// What bounds it: nothing alone.  One 32 x 32 x 128 product per wavefront and tile is 8 matrix instructions
+// against 10 KB read from shared memory, about 90 other vector instructions (the scan of sixteen logits, the
+// channels' maxima, the lists) and a barrier; the matrix cores are busy 28 % of the cycles and vector
+// instructions issued on 39 %.  The keys stream 1.3 to 2 times from HBM (1.2 GB on 240 KV-heads at 15000
+// positions: 0.25 ms at the rate of a large copy).  240 KV-heads, 15000 positions, 256 rows each, K = 4: 4.37-4.5 ms
+// with every logit in double, 0.46-0.49 ms here (0.54 while every tile waited for a shared maximum over all
+// channels); the same with constants of up to 1000 in a channel.  Eight wavefronts: RB blocks of 32 rows
 // times KS = 8 / RB shares of a tile's keys, so that a few rows still use the whole work-group.
 constexpr int VH_OPEN = -1;
 constexpr int VF_THREADS = 512;
