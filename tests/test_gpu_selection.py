@@ -1,6 +1,6 @@
 """GPU test of the selection's ranking and slot assignment at the chunk counts where they change method, in
-the three places the selection runs: inside the anchor tiles' launch (up to 256 chunks here; several anchor
-heads and sequences, so that its arrivals chain), inside the tidal launch, and in kernels of its own.  Each
+the three places the selection runs: inside the anchor tiles' launch (several anchor heads and sequences, so
+that its arrivals chain), inside the tidal launch, and in kernels of its own.  Each
 case checks from the library's trace that the selection ran where it should.  The chunk scores that the step
 reports fix the selection exactly; residency and slot bytes follow from it."""
 import re
@@ -19,25 +19,29 @@ def _gpu():
 
 
 @pytest.mark.parametrize("mode", ["same", "next", "next_copies"])
-@pytest.mark.parametrize("big", [False, True], ids=["small", "large"])
-@pytest.mark.parametrize("n", [3, 64, 128, 129, 160, 161, 256, 257, 420, 421, 768, 769, 1000])
-def test_selection_follows_the_scores(n, big, mode, capfd, monkeypatch):
+@pytest.mark.parametrize("n,size", [(n, size) for n in (3, 64, 128, 129, 160, 161, 256, 257, 420, 421, 768, 769, 1000)
+                                    for size in ("small", "large")] + [(257, "wide"), (300, "wide")])
+def test_selection_follows_the_scores(n, size, mode, capfd, monkeypatch):
     import torch
     from paper_2608_22704_amd import wnw as W
     from tests.wnw_harness import log
-    log(f"[case] selection over {n} chunks, {mode}, {'many' if big else 'few'} anchor tiles")
-    # `large`: more anchor tiles than the chip holds at once, so that the selection has its own kernel
-    B, L, Hq, Hkv, cl, Tt, delta = (1 if big else 2), (80 if big else 3), 8, 4, 2, (5000 if big else 8), 3
+    log(f"[case] selection over {n} chunks, {mode}, {size}")
+    # `large`: more anchor tiles than the chip holds at once, so that the selection has its own kernel;
+    # `wide`: few anchor tiles beside many static ones, which hide a selection over more than 256 chunks
+    big = size == "large"
+    B, L, Tt = {"small": (2, 3, 8), "large": (1, 80, 5000), "wide": (1, 160, 8)}[size]
+    Hq, Hkv, cl, delta = 8, 4, 2, 3
     Ta, k = n * cl, max(1, n // 5)
     flags = {"same": 0, "next": W.WNW_F_SELECT_NEXT_STEP,
              "next_copies": W.WNW_F_SELECT_NEXT_STEP | W.WNW_F_RECALL_MEMCPY}[mode]
     # the arrays of 420 chunks and more do not fit the tidal launch's shared memory
     where = ("inside the tidal launch" if mode == "next_copies" and n < 420 else
-             "inside the anchor launch" if mode != "next_copies" and n <= 256 and not big else "before the tidal launch")
+             "inside the anchor launch" if mode != "next_copies" and not big and (n <= 256 or (size, mode) == ("wide", "next"))
+             else "before the tidal launch")
     g = torch.Generator(device="cuda").manual_seed(n)
     kv = [torch.randn((B, L, Hkv, Ta + Tt, 128), generator=g, device="cuda").bfloat16() for _ in range(2)]
     roles = np.full((L, Hkv), W.WNW_FIXED, np.uint8)
-    roles[:, 0] = W.WNW_ANCHOR
+    roles[: 3 if size == "wide" else L, 0] = W.WNW_ANCHOR
     roles[0, 1:3] = W.WNW_TIDAL
     pf = torch.rand((B, L, Hkv, Ta), generator=g, device="cuda")
     monkeypatch.setenv("WNW_LOG", "1")
